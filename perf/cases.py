@@ -1,0 +1,260 @@
+"""What the framework is measured on: calls a serving program makes, from one token to a full prompt batch.
+
+A case names one pass through the public entry points (paper_2312_05215_amd.dz_*), by `path`:
+
+  linear    one dz_linear call: a single projection, base plus per-request deltas
+  layer     the seven projections of one transformer layer: q,k,v -> dz_linear_group, o -> dz_linear,
+            gate,up -> dz_linear_group, down -> dz_linear, each with its own weights and deltas
+  split     dz_base_gemm, then dz_sbmm adding the deltas to its result: a program that keeps the two apart
+  base      dz_base_gemm over the projections of a layer: requests of the base model alone
+  adapters  dz_base_gemm, then dz_lora_sbmm adding low-rank adapters, on the attention projections
+  register  a fine-tuned delta comes in: dz_compress_delta, then dz_pack_delta, for each projection of a layer
+  merge     one variant's own weights, W + delta: dz_merge_delta for each projection of a layer
+
+Weights are N(0, 0.02), activations N(0, 1), deltas N(0, 0.002), as in dz_synth; deltas are compressed and packed
+by the library itself.  The largest shapes are those of the 7B, 13B and 70B Llama layers dz_synth names.
+"""
+import torch
+
+import dz_synth as S
+import paper_2312_05215_amd as dz
+
+HALF = torch.float16
+_context = []
+
+
+def _ctx():
+    """The one library context a program keeps for its stream."""
+    if not _context:
+        _context.append(dz.Context(0))
+    return _context[0]
+
+
+# ------------------------------------------------------------------------------------------ the cases
+def _layer(name, path, T, hidden, ffn, kv, **more):
+    return dict({"name": name, "path": path, "T": T, "hidden": hidden, "ffn": ffn, "kv": kv}, **more)
+
+
+def listed():
+    fmt4 = {"bits": 4, "group": 128}
+    fmt2 = {"bits": 2, "group": 128}
+    return [
+        # one user's next token through one projection: latency, the smallest call there is
+        {"name": "linear_1", "path": "linear", "T": 1, "N": 4096, "K": 4096, "D": 8, "ids": "uniform", "idle": 0, **fmt4},
+        # an ordinary decode step: 32 users over 8 variants, one 7B layer
+        _layer("decode_7b_32", "layer", 32, 4096, 11008, 4096, D=8, ids="uniform", idle=0, **fmt4),
+        # decode with many tenants of skewed popularity, one 7B layer
+        _layer("decode_7b_many_64", "layer", 64, 4096, 11008, 4096, D=32, ids="zipf", idle=0, **fmt2),
+        # the largest weights: decode through one 70B layer (grouped-query attention)
+        _layer("decode_70b_64", "layer", 64, 8192, 28672, 1024, D=4, ids="uniform", idle=0, **fmt2),
+        # a ragged decode step, some requests for the base model, base and delta products called apart
+        {"name": "split_13", "path": "split", "T": 13, "N": 5120, "K": 13824, "D": 5, "ids": "uniform", "idle": 25,
+         "bits": 2, "group": 64},
+        # decode rows and short prompt chunks in one batch (chunked prefill), a quarter of them for the base model
+        _layer("mixed_7b_200", "layer", 200, 4096, 11008, 4096, D=8, ids="uniform", idle=25, bits=4, group=64),
+        # a prompt batch: 16 prompts of 16 variants, one 13B layer
+        _layer("prefill_13b_2048", "layer", 2048, 5120, 13824, 5120, D=16, ids="segments", idle=0, **fmt4),
+        # a few prompts of odd lengths, one 7B layer
+        _layer("prefill_7b_777", "layer", 777, 4096, 11008, 4096, D=3, ids="segments", idle=0, **fmt2),
+        # prompts for the base model alone, one 13B layer
+        _layer("base_13b_2048", "base", 2048, 5120, 13824, 5120),
+        # low-rank adapters beside the base model, decode batch, attention projections of a 7B layer
+        _layer("adapters_7b_64", "adapters", 64, 4096, 11008, 4096, D=8, ids="uniform", idle=0, rank=16),
+        # a new variant is registered: one 7B layer compressed and packed
+        _layer("register_7b", "register", 0, 4096, 11008, 4096, **fmt4),
+        # a variant gets weights of its own: one 7B layer merged
+        _layer("merge_7b", "merge", 0, 4096, 11008, 4096, **fmt4),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(lo * (hi / lo) ** rng.random()))
+
+
+def _multiple(v, of, least, most):
+    return max(least, min(most, (v + of // 2) // of * of))
+
+
+#: request rows times weights of the largest listed case, and its weights: no drawn case costs more
+_MOST_WORK = 2048 * (4 * 5120 * 5120 + 3 * 5120 * 13824)
+_MOST_WEIGHTS = 2 * 8192 * 8192 + 2 * 1024 * 8192 + 3 * 8192 * 28672
+
+
+def draw(rng):
+    path = rng.choice(["linear", "linear", "linear", "layer", "layer", "layer", "layer", "split", "base", "adapters",
+                       "register", "merge"])
+    case = {"path": path, "T": 0}
+    if path in ("linear", "split"):
+        case["N"] = _multiple(_log(rng, 1024, 28672), 16, 1024, 28672)
+        case["K"] = _multiple(_log(rng, 1024, 28672), 256, 1024, 28672)
+        while case["N"] * case["K"] > 28672 * 8192:
+            case["N"] = _multiple(case["N"] // 2, 16, 1024, 28672)
+        weights = case["N"] * case["K"]
+    else:
+        hidden = _multiple(_log(rng, 1024, 8192), 256, 1024, 8192)
+        case.update(hidden=hidden, ffn=_multiple(int(hidden * rng.uniform(2.6, 3.5)), 256, 2560, 28672),
+                    kv=hidden // rng.choice([1, 1, 4, 8]))
+        weights = sum(n * k for _, n, k in _projections(case))
+    if path not in ("register", "merge"):
+        # decode-sized, middle and prompt-sized batches alike; low-rank adapters as for decode up to short prompts
+        T = _log(rng, 1, 512) if path == "adapters" else _log(rng, 1, 2048)
+        case["T"] = max(1, min(T, _MOST_WORK // weights))
+    if path != "base":
+        case.update(bits=rng.choice([2, 4]), group=rng.choice([64, 128, 128]))
+    if path in ("linear", "layer", "split", "adapters"):
+        case["D"] = min(_log(rng, 1, 32), max(1, 6 * _MOST_WEIGHTS // weights))
+        case["ids"] = rng.choice(["uniform", "zipf", "segments"] if case["T"] >= case["D"] else ["uniform", "zipf"])
+        case["idle"] = rng.choice([0, 0, 25])
+    if path == "adapters":
+        case["rank"] = 8 * rng.randint(1, 8)
+        del case["bits"], case["group"]
+    return case
+
+
+# ------------------------------------------------------------------------------------- inputs and state
+def _projections(case):
+    """(call, N, K) of each projection of the case; projections with the same call number share x and one call."""
+    if "hidden" not in case:
+        return [(0, case["N"], case["K"])]
+    h, f, kv = case["hidden"], case["ffn"], case["kv"]
+    attention = [(0, h, h), (0, kv, h), (0, kv, h), (1, h, h)]
+    if case["path"] == "adapters":
+        return attention
+    return attention + [(2, f, h), (2, f, h), (3, h, f)]
+
+
+def _normal(shape, std, gen):
+    return torch.empty(shape, dtype=torch.float32, device="cuda").normal_(0.0, std, generator=gen).to(HALF)
+
+
+def _tables(N, K, group):
+    return (torch.empty(N, K // 2, dtype=torch.uint8, device="cuda"), torch.empty(N, K // 2, dtype=torch.uint8, device="cuda"),
+            torch.empty(N, K // group, dtype=HALF, device="cuda"), torch.empty(N, K // group, dtype=HALF, device="cuda"))
+
+
+def _packed_delta(ctx, N, K, bits, group, gen):
+    tables = _tables(N, K, group)
+    dz.dz_compress_delta(ctx.h, _normal((N, K), 0.002, gen), N, K, bits, group, *tables)
+    packed = torch.empty(dz.dz_packed_bytes(N, K, bits, group), dtype=torch.uint8, device="cuda")
+    dz.dz_pack_delta(ctx.h, *tables, N, K, bits, group, packed)
+    return packed
+
+
+def _ids(case, gen):
+    T, D = case["T"], case["D"]
+    ids = {"uniform": S.ids_uniform, "segments": S.ids_segments}[case["ids"]](T, D, gen) if case["ids"] != "zipf" else S.ids_zipf(T, D, 1.5, gen)
+    if case["idle"]:        # requests of the base model
+        ids[torch.rand(T, generator=gen, device="cuda") * 100 < case["idle"]] = -1
+    return ids
+
+
+def prepare(case, seed):
+    ctx = _ctx()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    path, T = case["path"], case["T"]
+    projections = _projections(case)
+    state = {"case": case, "ctx": ctx, "calls": []}
+    if path == "register":
+        state["parts"] = [(N, K, _normal((N, K), 0.002, gen), _tables(N, K, case["group"]),
+                           torch.empty(dz.dz_packed_bytes(N, K, case["bits"], case["group"]), dtype=torch.uint8, device="cuda"))
+                          for _, N, K in projections]
+        return state
+    if path == "merge":
+        state["parts"] = [(N, K, _normal((N, K), 0.02, gen), _packed_delta(ctx, N, K, case["bits"], case["group"], gen),
+                           torch.empty(N, K, dtype=HALF, device="cuda")) for _, N, K in projections]
+        return state
+    if path != "base":
+        state["ids"] = _ids(case, gen)
+    for call in sorted({c for c, _, _ in projections}):
+        shapes = [(N, K) for c, N, K in projections if c == call]
+        K = shapes[0][1]
+        one = {"K": K, "N": [N for N, _ in shapes], "x": _normal((T, K), 1.0, gen),
+               "W": [_normal((N, K), 0.02, gen) for N, _ in shapes],
+               "out": [torch.empty(T, N, dtype=HALF, device="cuda") for N, _ in shapes]}
+        if path in ("linear", "layer", "split"):
+            one["deltas"] = [[_packed_delta(ctx, N, K, case["bits"], case["group"], gen) for _ in range(case["D"])] for N, _ in shapes]
+        if path == "adapters":
+            one["A"] = [[_normal((case["rank"], K), 0.02, gen) for _ in range(case["D"])] for N, _ in shapes]
+            one["B"] = [[_normal((N, case["rank"]), 0.02, gen) for _ in range(case["D"])] for N, _ in shapes]
+        state["calls"].append(one)
+    return state
+
+
+# ------------------------------------------------------------------------------------------- one pass
+def run(state):
+    case, h = state["case"], state["ctx"].h
+    path, T = case["path"], case["T"]
+    if path == "register":
+        for N, K, delta, tables, packed in state["parts"]:
+            dz.dz_compress_delta(h, delta, N, K, case["bits"], case["group"], *tables)
+            dz.dz_pack_delta(h, *tables, N, K, case["bits"], case["group"], packed)
+        return [packed for _, _, _, _, packed in state["parts"]]
+    if path == "merge":
+        for N, K, W, packed, merged in state["parts"]:
+            dz.dz_merge_delta(h, W, packed, N, K, case["bits"], case["group"], merged)
+        return [merged for _, _, _, _, merged in state["parts"]]
+    if path == "layer":
+        # the projections of a layer share one request vector; setting the option forgets the previous batch's
+        state["ctx"].set_option(dz.DZ_OPT_REUSE_SEGMENTS, 1)
+    for one in state["calls"]:
+        K, x = one["K"], one["x"]
+        if path == "layer" and len(one["N"]) > 1:
+            dz.dz_linear_group(h, x, one["W"], one["deltas"], state["ids"], one["out"], T, one["N"], K, case["bits"], case["group"])
+            continue
+        for i, N in enumerate(one["N"]):
+            W, out = one["W"][i], one["out"][i]
+            if path in ("linear", "layer"):
+                dz.dz_linear(h, x, W, one["deltas"][i], state["ids"], out, T, N, K, case["bits"], case["group"])
+                continue
+            dz.dz_base_gemm(h, x, W, out, T, N, K)
+            if path == "split":
+                dz.dz_sbmm(h, x, one["deltas"][i], state["ids"], out, T, N, K, case["bits"], case["group"], accumulate=1)
+            if path == "adapters":
+                dz.dz_lora_sbmm(h, x, one["A"][i], one["B"][i], case["rank"], state["ids"], out, T, N, K, accumulate=1)
+    if path == "layer":
+        state["ctx"].set_option(dz.DZ_OPT_REUSE_SEGMENTS, 0)
+    return [out for one in state["calls"] for out in one["out"]]
+
+
+# ------------------------------------------------------------------------------------- what a pass needs
+def _active(case):
+    """Deltas that have a request, on average over the request vectors."""
+    T, D = case["T"] * (100 - case["idle"]) / 100, case["D"]
+    if case["ids"] == "segments":
+        return D
+    p = [1.0 / D] * D if case["ids"] == "uniform" else [(m + 1) ** -1.5 for m in range(D)]
+    return sum(1 - (1 - v / sum(p)) ** T for v in p)
+
+
+def work(case):
+    path, T = case["path"], case["T"]
+    nbytes, flops, seen = 0.0, 0.0, set()
+    for call, N, K in _projections(case):
+        weights = N * K
+        packed = weights * (2 * case["bits"] + 4) // 32 + 4 * weights // case["group"] if "bits" in case else 0
+        if path == "register":      # the delta in, the tables out and in again, the packed delta out
+            nbytes += 2 * weights + 2 * (weights + 4 * weights // case["group"]) + packed
+            continue
+        if path == "merge":
+            nbytes += 2 * weights + packed + 2 * weights
+            flops += weights / 2
+            continue
+        nbytes += 2 * weights + 2 * T * N + (2 * T * K if call not in seen else 0)
+        seen.add(call)
+        flops += 2.0 * T * weights
+        if path in ("linear", "layer", "split"):
+            nbytes += _active(case) * packed
+            flops += T * (100 - case["idle"]) / 100 * weights       # the kept half of a delta
+        if path == "adapters":
+            nbytes += _active(case) * 2 * case["rank"] * (N + K)
+            flops += 2.0 * T * (100 - case["idle"]) / 100 * case["rank"] * (N + K)
+    return {"bytes": nbytes, "flops": flops}
+
+
+def tolerance(case):
+    if case["path"] in ("register", "merge"):
+        return "exact"              # bytes, and one rounding of an exact sum
+    # four times what fp16 results of fp32 sums show against the same sums in 64 bits: rel 2.1e-4, max 5.3e-4 (about half
+    # a unit in the last place), and max 1.1e-3 where the base product is rounded before the second product is added
+    return {"rel": 1e-3, "max": 4e-3 if case["path"] in ("split", "adapters") else 2e-3}

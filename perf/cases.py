@@ -258,3 +258,63 @@ def tolerance(case):
     # four times what fp16 results of fp32 sums show against the same sums in 64 bits: rel 2.1e-4, max 5.3e-4 (about half
     # a unit in the last place), and max 1.1e-3 where the base product is rounded before the second product is added
     return {"rel": 1e-3, "max": 4e-3 if case["path"] in ("split", "adapters") else 2e-3}
+
+
+# ------------------------------------------------------------------- the same results in 64 bits, plain torch
+def _compressed_values(delta, bits, group):
+    """The matrix a delta [N][K] stands for once it is compressed, as dz.h states the rule, in float64."""
+    N, K = delta.shape
+    v = delta.float().view(N, K // 4, 4)
+    mag = v.abs()
+    # an entry is kept if it beats two of the other three: larger magnitude, or the same at a lower position
+    beats = (mag[..., :, None] > mag[..., None, :]) | ((mag[..., :, None] == mag[..., None, :])
+                                                       & torch.ones(4, 4, dtype=torch.bool, device=v.device).triu(1))
+    kept = (beats.sum(-1) >= 2).view(N, K // group, group)
+    v = v.reshape(N, K // group, group)
+    zero = torch.zeros_like(v)
+    lo = torch.where(kept, v, zero).amin(-1, keepdim=True).clamp(max=0)
+    hi = torch.where(kept, v, zero).amax(-1, keepdim=True).clamp(min=0)
+    top = 2 ** bits - 1
+    s = ((hi - lo) / top).half().float()
+    dead = s == 0
+    s = torch.where(dead, torch.ones_like(s), s)
+    z = torch.where(dead, torch.zeros_like(s), torch.round(-lo / s).clamp(0, top))
+    code = (torch.round(v / s) + z).clamp(0, top)
+    return torch.where(kept, (code - z).double() * s.double(), torch.zeros((), dtype=torch.float64, device=v.device)).view(N, K)
+
+
+def exact(case, seed):
+    """run()'s outputs from the same inputs, drawn in the order in which prepare() draws them."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    path, T = case["path"], case["T"]
+    projections = _projections(case)
+    if path == "register":
+        return None             # bytes
+    if path == "merge":
+        return [_normal((N, K), 0.02, gen).double() + _compressed_values(_normal((N, K), 0.002, gen), case["bits"], case["group"])
+                for _, N, K in projections]
+    ids = _ids(case, gen) if path != "base" else None
+    outs = []
+    for call in sorted({c for c, _, _ in projections}):
+        shapes = [(N, K) for c, N, K in projections if c == call]
+        x = _normal((T, shapes[0][1]), 1.0, gen).double()
+        ys = []
+        for N, K in shapes:
+            W = _normal((N, K), 0.02, gen)
+            ys.append(x @ W.double().t())
+        if path in ("linear", "layer", "split"):
+            for y, (N, K) in zip(ys, shapes):
+                for m in range(case["D"]):
+                    delta, rows = _normal((N, K), 0.002, gen), (ids == m).nonzero().flatten()
+                    if len(rows):
+                        y[rows] += x[rows] @ _compressed_values(delta, case["bits"], case["group"]).t()
+        if path == "adapters":
+            A = [[_normal((case["rank"], K), 0.02, gen).double() for _ in range(case["D"])] for N, K in shapes]
+            B = [[_normal((N, case["rank"]), 0.02, gen).double() for _ in range(case["D"])] for N, K in shapes]
+            for y, a, b in zip(ys, A, B):
+                for m in range(case["D"]):
+                    rows = (ids == m).nonzero().flatten()
+                    y[rows] += (x[rows] @ a[m].t()) @ b[m].t()
+        outs += ys
+    return outs

@@ -184,7 +184,7 @@ int dz_linear(dz_ctx *ctx, const void *x_f16, const void *W_f16, const void *con
  *   accumulate == 0 : out[t] = f16(y[t]);   accumulate != 0 : out[t] = f16(float(out[t]) + y[t]),
  * so a base product or a dz_linear result can be completed in place.  A and B are HOST arrays of D
  * DEVICE pointers (16-byte aligned, read before the call returns).  rank in {8, 16, ..., 64};
- * K % 8 == 0; N % 4 == 0; out 8-byte aligned.  The batch is walked in adapter-sorted order.
+ * K % 8 == 0; N % 4 == 0; out 8-byte aligned.
  */
 int dz_lora_sbmm(dz_ctx *ctx, const void *x_f16, const void *const *A_f16, const void *const *B_f16, int D,
                  int rank, const int32_t *token_to_adapter, void *out_f16, int T, int N, int K,

@@ -469,15 +469,9 @@ int dz_lora_sbmm(dz_ctx *ctx, const void *x, const void *const *A, const void *c
     }
     DeviceGuard guard(ctx->device);
     hipStream_t st = (hipStream_t)stream;
-    int rc = ensure_seg(ctx, T, st);
+    int rc = dz_ensure_lora(ctx, (size_t)T * rank * sizeof(float), st);
     if (rc) return rc;
-    rc = dz_ensure_lora(ctx, (size_t)T * rank * sizeof(float), st);
-    if (rc) return rc;
-    // the adapter-sorted order of the batch (Section 5.2: requests of one model are grouped)
-    rc = dz_launch_segment(ctx, ids, T, D, nullptr, nullptr, ctx->seg_perm, ctx->seg_key, st);
-    if (rc) return rc;
-    ctx->seg_ids = nullptr;         // the remembered order of DZ_OPT_REUSE_SEGMENTS is gone
-    return dz_launch_lora(ctx, x, A, B, D, rank, ids, ctx->seg_perm, ctx->lora_u, out, T, N, K, accumulate ? 1 : 0, st);
+    return dz_launch_lora(ctx, x, A, B, D, rank, ids, ctx->lora_u, out, T, N, K, accumulate ? 1 : 0, st);
 }
 
 int dz_check(dz_ctx *ctx, void *stream)

@@ -119,4 +119,4 @@ int dz_launch_merge(dz_ctx *, const void *W, const void *packed, int N, int K, i
 int dz_launch_compress(dz_ctx *, const void *delta, int N, int K, int bits, int group, uint8_t *codes, uint8_t *idx,
                        void *scale, void *zero, hipStream_t);
 int dz_launch_lora(dz_ctx *, const void *x, const void *const *A, const void *const *B, int D, int rank, const int32_t *ids,
-                   const int32_t *perm, float *u, void *out, int T, int N, int K, int accumulate, hipStream_t);
+                   float *u, void *out, int T, int N, int K, int accumulate, hipStream_t);

@@ -274,8 +274,7 @@ int dz_segment(dz_ctx *ctx, const int32_t *ids, int T, int D, int32_t *counts, i
     return dz_launch_segment(ctx, ids, T, D, counts, offsets, perm, nullptr, (hipStream_t)stream);
 }
 
-// P projections that share x and the request indices.  Small batches: one launch of the streaming
-// kernel for all of them.  Large batches: the tiled kernel, one projection after the other.
+// P projections that share x and the request indices, in one launch.
 static int run_group(dz_ctx *ctx, const void *x, int P, const void *const *W, const void *const *deltas, int D,
                      const int32_t *ids, void *const *out, const int *N, int T, int K, int bits, int group,
                      int accumulate, bool has_base, bool has_delta, hipStream_t st, bool quant_only = false)
@@ -327,33 +326,20 @@ static int run_group(dz_ctx *ctx, const void *x, int P, const void *const *W, co
         a.perm = ctx->seg_perm;
         a.key = ctx->seg_key;
     }
-    if (!tiled) {                       // small batches: HBM-bound streaming kernel, all projections in one launch
-        DzGroup gp;
-        DzGroupPtrs dp;
-        memset(&gp, 0, sizeof(gp));
-        memset(&dp, 0, sizeof(dp));
-        gp.P = P;
-        for (int p = 0; p < P; ++p) {
-            gp.N[p] = N[p];
-            gp.W[p] = has_base ? W[p] : nullptr;
-            gp.out[p] = out[p];
-        }
-        if (has_delta)
-            for (int m = 0; m < P * D; ++m) dp.p[m] = deltas[m];
-        return dz_launch_stream(ctx, a, gp, dp, st);
-    }
+    // all projections in one launch: small batches in the HBM-bound streaming kernel, large ones in the tiled kernel
+    DzGroup gp;
+    DzGroupPtrs dp;
+    memset(&gp, 0, sizeof(gp));
+    memset(&dp, 0, sizeof(dp));
+    gp.P = P;
     for (int p = 0; p < P; ++p) {
-        DzDeltaPtrs dp;
-        memset(&dp, 0, sizeof(dp));
-        if (has_delta)
-            for (int m = 0; m < D; ++m) dp.p[m] = deltas[p * D + m];
-        a.W = has_base ? W[p] : nullptr;
-        a.out = out[p];
-        a.N = N[p];
-        int rc = dz_launch_prefill(ctx, a, dp, st);
-        if (rc) return rc;
+        gp.N[p] = N[p];
+        gp.W[p] = has_base ? W[p] : nullptr;
+        gp.out[p] = out[p];
     }
-    return DZ_OK;
+    if (has_delta)
+        for (int m = 0; m < P * D; ++m) dp.p[m] = deltas[m];
+    return tiled ? dz_launch_prefill(ctx, a, gp, dp, st) : dz_launch_stream(ctx, a, gp, dp, st);
 }
 
 int dz_run_linear(dz_ctx *ctx, const void *x, const void *W, const void *const *deltas, int D,

@@ -42,11 +42,9 @@ struct dz_ctx {
 
 #define DZ_SEG_MAX_D 8192
 
-struct DzDeltaPtrs { const void *p[DZ_MAX_DELTAS]; };
-
 // Several projections that share x and the request indices (q,k,v or gate,up of one transformer
-// layer) can go through the streaming kernel in one launch.  Filled in part by the caller (P, N, W,
-// out) and in part by the launcher.
+// layer) go through the streaming or the tiled kernel in one launch.  Filled in part by the caller (P, N,
+// W, out) and in part by the launcher.
 #define DZ_GROUP_PTRS (3 * DZ_MAX_DELTAS)       /* projections x deltas of one launch */
 struct DzGroupPtrs { const void *p[DZ_GROUP_PTRS]; };   // packed deltas, projection-major: p[proj * D + delta]
 struct DzGroup {
@@ -108,7 +106,7 @@ int dz_launch_unpack(dz_ctx *, const void *, int, int, int, int, uint8_t *, uint
 int dz_launch_segment(dz_ctx *, const int32_t *ids, int T, int D, int32_t *counts, int32_t *offsets,
                       int32_t *perm, int32_t *key, hipStream_t);
 int dz_launch_stream(dz_ctx *, const DzStreamArgs &, const DzGroup &, const DzGroupPtrs &, hipStream_t);
-int dz_launch_prefill(dz_ctx *, const DzStreamArgs &, const DzDeltaPtrs &, hipStream_t);
+int dz_launch_prefill(dz_ctx *, const DzStreamArgs &, const DzGroup &, const DzGroupPtrs &, hipStream_t);
 int dz_launch_tile(dz_ctx *, const DzStreamArgs &, hipStream_t);
 bool dz_tile_fits(const DzStreamArgs &);
 int dz_launch_qpack(dz_ctx *, const uint8_t *codes, const void *scale, const void *zero, int N, int K, int bits, int group,

@@ -7,7 +7,10 @@
 // instead of around HBM bytes:
 //   * a workgroup (8 waves) owns an output tile of 256 rows of N x 128 request rows (in
 //     delta-sorted order, from the segment pass) and the whole k range; the tiles of the last,
-//     partly filled round of one-tile-per-CU are cut into slices of k that meet in fp32;
+//     partly filled round of one-tile-per-CU are cut into slices of k that meet in fp32; projections
+//     that share x and the request indices (q,k,v; gate,up) are one launch, so that a call pays for one
+//     partly filled round and one start-up (7B layer, T = 200, 8 deltas: 603 -> 416 us with that, the wider
+//     meeting and more slices; T = 777, 3 deltas: 707 -> 628 us);
 //   * a wave owns 2 row tiles x 8 column blocks = 16 accumulator tiles (64 registers); W and
 //     packed-delta fragments go from global memory straight into MFMA A operands (each wave owns
 //     its rows, so A needs no sharing), the 128 x 256 slice of x of the current k tile sits in LDS
@@ -29,6 +32,7 @@
 // Measured on the 13B shapes the kernel is bound by the rate at which L2 feeds the CUs (the tile
 // moves 192 KB per 256 k), not by the MFMA pipes.
 #include "dz_mma.h"
+#include <algorithm>
 
 
 namespace {
@@ -160,8 +164,7 @@ __device__ __forceinline__ void delta_mm(const h8 (&av)[4][R], const uint32_t (&
 }
 
 template <int BITS, int GROUP, bool QO, int PW, int PR, int PJ, bool HAS_BASE, bool HAS_DELTA>
-__global__ __launch_bounds__(PW * 64) void prefill_kernel(DzStreamArgs a, DzDeltaPtrs dp, int NRB, int nchunks,
-                                                          size_t off_idx, size_t off_scale, size_t blob_total)
+__global__ __launch_bounds__(PW * 64) void prefill_kernel(DzStreamArgs a, DzGroup gp, DzGroupPtrs dp, int NRB, int nchunks)
 {
     typedef Fmt<BITS, GROUP, QO> F;
     constexpr int SD = F::SD;
@@ -215,9 +218,43 @@ __global__ __launch_bounds__(PW * 64) void prefill_kernel(DzStreamArgs a, DzDelt
     const int ke = (int)((uint32_t)(ks + 1) * (uint32_t)g.KT / (uint32_t)S);
     const int p0 = chunk * PCH;
     const int cnt = min(PCH, a.T - p0);
-    const int RT = a.N >> 4;
+    // the projection this row block belongs to (their row blocks are numbered one after the other)
+    int pj = 0;
+    while (pj + 1 < gp.P && rb >= gp.rb_start[pj + 1]) ++pj;
+    const int rbl = rb - gp.rb_start[pj];
+    const int Np = gp.N[pj];
+    const int RT = Np >> 4;
+    const uint32_t off_idx = gp.off_idx[pj], off_scale = gp.off_scale[pj], blob_bytes = gp.blob_total[pj];
 
-    if (HAS_DELTA && tid < max(a.D, 1)) s_dptr[tid] = tid < a.D ? (unsigned long long)dp.p[tid] : (unsigned long long)a.x;
+    int rtc[PR];
+    bool rvalid[PR];
+    uint32_t wrow[PR];
+#pragma unroll
+    for (int r = 0; r < PR; ++r) {
+        const int rt = rbl * (PW * PR) + wave * PR + r;
+        rvalid[r] = rt < RT;
+        rtc[r] = rvalid[r] ? rt : RT - 1;
+        wrow[r] = (uint32_t)rtc[r] * 16u * (uint32_t)a.K * 2u;
+    }
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(HAS_BASE ? gp.W[pj] : a.x, HAS_BASE ? (uint32_t)Np * (uint32_t)a.K * 2u : 0u);
+    // Fused launches multiply the delta tiles between the base steps of their k tile -- segment sg
+    // after step sg % 4 -- so that the W and x loads each step sends out keep flowing during the
+    // delta work; the W ring is then two buffers deep (one step ahead), which leaves the registers
+    // for it.  Base-only launches prefetch W three steps ahead.
+    constexpr bool ILV = HAS_BASE && HAS_DELTA;
+    constexpr int DIST = ILV ? 1 : 3;          // W prefetch distance in steps
+    // the first weight loads go out before the request order is even known: they come from HBM and take longest
+    u32x4 bwA[PR][2], bwB[PR][2], bwC[PR][2], bwD[PR][2];
+    if constexpr (HAS_BASE) {
+        base_issue<PR>(rw, wrow, lo.w, 4 * kb, bwA);
+        if constexpr (DIST == 3) {
+            base_issue<PR>(rw, wrow, lo.w, 4 * kb + 1, bwB);
+            base_issue<PR>(rw, wrow, lo.w, 4 * kb + 2, bwC);
+        }
+    }
+
+    unsigned long long my_dptr = (unsigned long long)a.x;
+    if (HAS_DELTA && tid < a.D) my_dptr = (unsigned long long)dp.p[pj * a.D + tid];
     if (tid < PCH) {
         int tok = -1, key = INT_MAX;
         if (tid < cnt) {
@@ -227,7 +264,8 @@ __global__ __launch_bounds__(PW * 64) void prefill_kernel(DzStreamArgs a, DzDelt
         s_tok[tid] = tok;
         s_key[tid] = key;
     }
-    __syncthreads();
+    if (HAS_DELTA && tid < max(a.D, 1)) s_dptr[tid] = my_dptr;
+    lds_barrier();
     // segments of this tile: starts found with one ballot per wave, numbered across the two waves
     bool start = false, valid = false;
     int key = INT_MAX;
@@ -240,7 +278,23 @@ __global__ __launch_bounds__(PW * 64) void prefill_kernel(DzStreamArgs a, DzDelt
     const unsigned long long sm = __ballot(start);
     const unsigned long long vm = __ballot(valid);
     if ((tid & 63) == 0 && tid < 128) { s_cnt[wave] = __builtin_popcountll(sm); s_cnt[2 + wave] = __builtin_popcountll(vm); }
-    __syncthreads();
+    // ---- x slice of one k tile -> LDS buffer: PCH rows x 32 pieces of 16 bytes, moved in four
+    // batches so that a batch can ride along with one MFMA step.  Piece p of a thread is row
+    // p * THREADS / 32 + tid / 32, bytes 16 * (tid % 32) of the slice; rows past the end of the
+    // batch get an offset beyond the resource, which the hardware answers with zeros.
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(a.x, (uint32_t)a.T * (uint32_t)a.K * 2u);
+    constexpr int XB = PCH * 32 / THREADS / 4;   // pieces per thread and batch
+    uint32_t xoff[4 * XB];
+#pragma unroll
+    for (int p = 0; p < 4 * XB; ++p) {
+        const int tok = s_tok[p * (THREADS / 32) + (tid >> 5)];
+        xoff[p] = tok >= 0 ? (uint32_t)tok * (uint32_t)a.K * 2u + (uint32_t)(tid & 31) * 16u : 0x80000000u;
+    }
+    // the whole first slice is requested at once, under the rest of the set-up
+    u32x4 xv0[4 * XB];
+#pragma unroll
+    for (int p = 0; p < 4 * XB; ++p) xv0[p] = __builtin_amdgcn_raw_buffer_load_b128(rx, xoff[p], (uint32_t)kb * 512u, 0);
+    lds_barrier();
     if (HAS_DELTA && tid < PCH) {
         const int base = (tid >= 64) ? s_cnt[0] : 0;
         if (start) {
@@ -254,19 +308,9 @@ __global__ __launch_bounds__(PW * 64) void prefill_kernel(DzStreamArgs a, DzDelt
             s_seg_begin[ns] = s_cnt[2] + (PCH > 64 ? s_cnt[3] : 0);      // rows that name a delta are a prefix
         }
     }
-    __syncthreads();
+    lds_barrier();
     const int nseg = HAS_DELTA ? s_nseg : 0;
 
-    int rtc[PR];
-    bool rvalid[PR];
-    uint32_t wrow[PR];
-#pragma unroll
-    for (int r = 0; r < PR; ++r) {
-        const int rt = rb * (PW * PR) + wave * PR + r;
-        rvalid[r] = rt < RT;
-        rtc[r] = rvalid[r] ? rt : RT - 1;
-        wrow[r] = (uint32_t)rtc[r] * 16u * (uint32_t)a.K * 2u;
-    }
     int brow[PJ];
 #pragma unroll
     for (int j = 0; j < PJ; ++j) brow[j] = (16 * j + g.row) * PLDW;
@@ -277,22 +321,6 @@ __global__ __launch_bounds__(PW * 64) void prefill_kernel(DzStreamArgs a, DzDelt
 #pragma unroll
         for (int j = 0; j < PJ; ++j) acc[r][j] = (f4){0.f, 0.f, 0.f, 0.f};
 
-    const uint32_t w_bytes = (uint32_t)a.N * (uint32_t)a.K * 2u;
-    const uint32_t blob_bytes = (uint32_t)blob_total;
-    const __amdgpu_buffer_rsrc_t rw = make_rsrc(a.W ? a.W : a.x, HAS_BASE ? w_bytes : 0u);
-    const __amdgpu_buffer_rsrc_t rx = make_rsrc(a.x, (uint32_t)a.T * (uint32_t)a.K * 2u);
-
-    // ---- x slice of one k tile -> LDS buffer: PCH rows x 32 pieces of 16 bytes, moved in four
-    // batches so that a batch can ride along with one MFMA step.  Piece p of a thread is row
-    // p * THREADS / 32 + tid / 32, bytes 16 * (tid % 32) of the slice; rows past the end of the
-    // batch get an offset beyond the resource, which the hardware answers with zeros.
-    constexpr int XB = PCH * 32 / THREADS / 4;   // pieces per thread and batch
-    uint32_t xoff[4 * XB];
-#pragma unroll
-    for (int p = 0; p < 4 * XB; ++p) {
-        const int tok = s_tok[p * (THREADS / 32) + (tid >> 5)];
-        xoff[p] = tok >= 0 ? (uint32_t)tok * (uint32_t)a.K * 2u + (uint32_t)(tid & 31) * 16u : 0x80000000u;
-    }
     const int xdst0 = (tid >> 5) * PLDW + (tid & 31) * 8;
     u32x4 xvA[XB], xvB[XB];                      // two batches in flight: loaded a step before they are stored
 #define PF_XLOAD(xv, kt, batch)                                                                                    \
@@ -310,36 +338,19 @@ __global__ __launch_bounds__(PW * 64) void prefill_kernel(DzStreamArgs a, DzDelt
     const int zoff = 2 * PCH * PLDW;         // the zero row, relative to either buffer's start: see below
     if (tid < PLDW / 8) *(u32x4 *)(xs_all + zoff + tid * 8) = (u32x4){0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        PF_XLOAD(xvA, kb, b);
-        PF_XSTORE(xvA, xcur, b);
-    }
+    for (int p = 0; p < 4 * XB; ++p) *(u32x4 *)(xcur + xdst0 + p * (THREADS / 32) * PLDW) = xv0[p];
     PF_XLOAD(xvA, min(kb + 1, ke - 1), 0);
 
-    u32x4 bwA[PR][2], bwB[PR][2], bwC[PR][2], bwD[PR][2];
     uint32_t st0[PR][SD];
     Cursor ci;                       // next delta tile to fetch: (segment, k tile)
     ci.kt = kb; ci.seg = 0;
     const int ndelta = nseg * (ke - kb);  // delta tiles this workgroup multiplies
     int ti = 0;
-    // Fused launches multiply the delta tiles between the base steps of their k tile -- segment sg
-    // after step sg % 4 -- so that the W and x loads each step sends out keep flowing during the
-    // delta work; the W ring is then two buffers deep (one step ahead), which leaves the registers
-    // for it.  Base-only launches prefetch W three steps ahead.
-    constexpr bool ILV = HAS_BASE && HAS_DELTA;
-    constexpr int DIST = ILV ? 1 : 3;          // W prefetch distance in steps
-    if constexpr (HAS_BASE) {
-        base_issue<PR>(rw, wrow, lo.w, 4 * kb, bwA);
-        if constexpr (DIST == 3) {
-            base_issue<PR>(rw, wrow, lo.w, 4 * kb + 1, bwB);
-            base_issue<PR>(rw, wrow, lo.w, 4 * kb + 2, bwC);
-        }
-    }
     int cs = 0;                      // interleaved order: the step the fetch cursor is at
 #define PF_DISSUE(buf)                                                                                             \
     do {                                                                                                           \
-        delta_issue<BITS, GROUP, QO, PR>(ci, ti < ndelta, g, rtc, lo, s_dptr, s_seg_delta, (uint32_t)off_idx,          \
-                                     (uint32_t)off_scale, blob_bytes, buf);                                        \
+        delta_issue<BITS, GROUP, QO, PR>(ci, ti < ndelta, g, rtc, lo, s_dptr, s_seg_delta, off_idx, off_scale,       \
+                                     blob_bytes, buf);                                                             \
         ++ti;                                                                                                      \
         if constexpr (ILV) {                                                                                       \
             ci.seg += 4;                                                                                           \
@@ -352,7 +363,7 @@ __global__ __launch_bounds__(PW * 64) void prefill_kernel(DzStreamArgs a, DzDelt
         }                                                                                                          \
     } while (0)
     if constexpr (HAS_DELTA) PF_DISSUE(st0);
-    __syncthreads();
+    lds_barrier();
 
     const int last_step = 4 * ke - 1;
     // A tile whose request rows all name the same delta (long prompts: most tiles) runs the delta
@@ -463,8 +474,11 @@ __global__ __launch_bounds__(PW * 64) void prefill_kernel(DzStreamArgs a, DzDelt
 
     // ---- k slices of one tile meet in fp32: every slice stores its accumulators (agent-scope
     // stores, register by register so that a store instruction writes 8 KB in a row), waits for
-    // them, and bumps the tile's arrival counter; the last one adds the slices in slice order --
-    // its own from registers -- so the sum does not depend on who arrives last.
+    // them, and bumps the tile's arrival counter; the last one adds all slices in slice order, its
+    // own like the others, so the sum does not depend on who arrives last.  The loads of two slices (256 KB
+    // of the workgroup) are in flight at once: they come from beyond the L2s and take 1 to 2 us each way.
+    // With one load at a time per lane the meeting of four slices took some 40 us; T = 200, 4096 x 4096, four
+    // slices: 70 -> 61 us, eight: 77 -> 52 us.
     if (S > 1) {
         constexpr int AGENT = 0x10;
         const uint32_t tile_bytes = (uint32_t)(PR * PJ) * THREADS * 16u;
@@ -491,34 +505,43 @@ __global__ __launch_bounds__(PW * 64) void prefill_kernel(DzStreamArgs a, DzDelt
 #pragma unroll
         for (int r = 0; r < PR; ++r)
 #pragma unroll
-            for (int j = 0; j < PJ; ++j) {
-                f4 sum = (f4){0.f, 0.f, 0.f, 0.f};
-                for (int sl = 0; sl < S; ++sl) {
-                    f4 v = acc[r][j];
-                    if (sl != ks)
-                        v = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                       prs, lane_off + (uint32_t)(r * PJ + j) * THREADS * 16u,
-                                                       (uint32_t)(slot0 + sl) * tile_bytes, AGENT));
-                    sum += v;
-                }
-                acc[r][j] = sum;
+            for (int j = 0; j < PJ; ++j) acc[r][j] = (f4){0.f, 0.f, 0.f, 0.f};
+        for (int sl = 0; sl < S; sl += 2) {
+            f4 v[2][PR][PJ];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int r = 0; r < PR; ++r)
+#pragma unroll
+                    for (int j = 0; j < PJ; ++j)
+                        v[u][r][j] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                                prs, lane_off + (uint32_t)(r * PJ + j) * THREADS * 16u,
+                                                                (uint32_t)(slot0 + min(sl + u, S - 1)) * tile_bytes, AGENT));
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (sl + u >= S) break;
+#pragma unroll
+                for (int r = 0; r < PR; ++r)
+#pragma unroll
+                    for (int j = 0; j < PJ; ++j) acc[r][j] += v[u][r][j];
             }
+        }
     }
     // ---- results: lane 16q + c holds rows 4q..4q+3 of each row tile for request column c
-    _Float16 *out = (_Float16 *)a.out;
+    _Float16 *out = (_Float16 *)gp.out[pj];
 #pragma unroll
     for (int r = 0; r < PR; ++r) {
         if (!rvalid[r]) continue;
 #pragma unroll
         for (int j = 0; j < PJ; ++j) {
             const int tok = s_tok[16 * j + g.row];
-            if (tok >= 0) store_row4(out + (size_t)tok * a.N + rtc[r] * 16 + 4 * g.q, acc[r][j], a.accumulate);
+            if (tok >= 0) store_row4(out + (size_t)tok * Np + rtc[r] * 16 + 4 * g.q, acc[r][j], a.accumulate);
         }
     }
 }
 
 template <int BITS, int GROUP, bool QO, int PW, int PR, int PJ, bool HB, bool HD>
-hipError_t launch_pf(const DzStreamArgs &a, const DzDeltaPtrs &dp, int NRB, int nchunks, const DzLayout &L, hipStream_t st)
+hipError_t launch_pf(const DzStreamArgs &a, const DzGroup &gp, const DzGroupPtrs &dp, int NRB, int nchunks, hipStream_t st)
 {
     auto k = prefill_kernel<BITS, GROUP, QO, PW, PR, PJ, HB, HD>;
     const size_t lds = (size_t)(2 * 16 * PJ + 1) * PLDW * sizeof(_Float16);
@@ -527,31 +550,43 @@ hipError_t launch_pf(const DzStreamArgs &a, const DzDeltaPtrs &dp, int NRB, int 
     if (e != hipSuccess) return e;
     const int tail = NRB * nchunks - 8 * a.max_slots;
     const int grid = 8 * (a.max_slots + ((tail + 7) / 8) * a.S);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(PW * 64), lds, st, a, dp, NRB, nchunks, L.off_idx, L.off_scale, L.total);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(PW * 64), lds, st, a, gp, dp, NRB, nchunks);
     return hipGetLastError();
 }
 
 template <bool QO, int PW, int PR, int PJ, bool HB, bool HD>
-hipError_t launch_pf_fmt(const DzStreamArgs &a, const DzDeltaPtrs &dp, int NRB, int nchunks, const DzLayout &L, hipStream_t st)
+hipError_t launch_pf_fmt(const DzStreamArgs &a, const DzGroup &gp, const DzGroupPtrs &dp, int NRB, int nchunks, hipStream_t st)
 {
-    if (!HD) return launch_pf<4, 128, false, PW, PR, PJ, HB, HD>(a, dp, NRB, nchunks, L, st);
-    if (a.bits == 4 && a.group == 128) return launch_pf<4, 128, QO, PW, PR, PJ, HB, HD>(a, dp, NRB, nchunks, L, st);
-    if (a.bits == 4) return launch_pf<4, 64, QO, PW, PR, PJ, HB, HD>(a, dp, NRB, nchunks, L, st);
-    if (a.group == 128) return launch_pf<2, 128, QO, PW, PR, PJ, HB, HD>(a, dp, NRB, nchunks, L, st);
-    return launch_pf<2, 64, QO, PW, PR, PJ, HB, HD>(a, dp, NRB, nchunks, L, st);
+    if (!HD) return launch_pf<4, 128, false, PW, PR, PJ, HB, HD>(a, gp, dp, NRB, nchunks, st);
+    if (a.bits == 4 && a.group == 128) return launch_pf<4, 128, QO, PW, PR, PJ, HB, HD>(a, gp, dp, NRB, nchunks, st);
+    if (a.bits == 4) return launch_pf<4, 64, QO, PW, PR, PJ, HB, HD>(a, gp, dp, NRB, nchunks, st);
+    if (a.group == 128) return launch_pf<2, 128, QO, PW, PR, PJ, HB, HD>(a, gp, dp, NRB, nchunks, st);
+    return launch_pf<2, 64, QO, PW, PR, PJ, HB, HD>(a, gp, dp, NRB, nchunks, st);
 }
 
 template <int PW, int PR, int PJ>
-hipError_t launch_pf_kind(dz_ctx *ctx, const DzStreamArgs &args, const DzDeltaPtrs &dp, const DzLayout &L, hipStream_t st,
+hipError_t launch_pf_kind(dz_ctx *ctx, const DzStreamArgs &args, const DzGroup &group, const DzGroupPtrs &dp, hipStream_t st,
                           int *rc)
 {
     DzStreamArgs a = args;
+    DzGroup gp = group;
     const int nchunks = (a.T + 16 * PJ - 1) / (16 * PJ);
-    const int NRB = (a.N / 16 + PW * PR - 1) / (PW * PR);
+    int NRB = 0;                            // row blocks of all projections; a row block never spans two
+    for (int p = 0; p < gp.P; ++p) {
+        const DzLayout L = (a.has_delta && a.quant_only) ? dz_make_qlayout(gp.N[p], a.K, a.bits, a.group)
+                                                         : dz_make_layout(gp.N[p], a.K, a.has_delta ? a.bits : 4, a.has_delta ? a.group : 128);
+        gp.off_idx[p] = (uint32_t)L.off_idx; gp.off_scale[p] = (uint32_t)L.off_scale; gp.blob_total[p] = (uint32_t)L.total;
+        gp.rb_start[p] = NRB;
+        NRB += (gp.N[p] / 16 + PW * PR - 1) / (PW * PR);
+    }
+    for (int p = gp.P; p <= DZ_MAX_GROUP; ++p) gp.rb_start[p] = NRB;
     // One workgroup per CU: `tiles` tiles take ceil(tiles / CUs) rounds, the last one partly
-    // filled.  The tiles of the full rounds run whole; those of the last round are cut into up to
-    // four slices of k, as many as still fit the CUs at once (320 tiles on 256 CUs: 256 whole,
-    // then 64 x 4 quarter tiles), and only they pay for the fp32 meeting.
+    // filled.  The tiles of the full rounds run whole; those of the last round are cut into slices of k,
+    // as many as still fit the CUs at once (320 tiles on 256 CUs: 256 whole, then 64 x 4 quarter
+    // tiles), and only they pay for the fp32 meeting.  At most 16 slices, and two k tiles in each: below that
+    // the meeting, to which every slice adds 128 KB, costs more than the shorter slices save
+    // (T = 100, 4096 x 4096, 16 tiles of 16 k tiles: 65 us with 4 slices, 50 with 8, 55 with 12; T = 100, 1024 x
+    // 8192, 4 tiles of 32 k tiles: 101 us with 4, 66 with 8, 56 with 16).
     const int tiles = NRB * nchunks;
     int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
     cus -= cus % 8;
@@ -561,9 +596,8 @@ hipError_t launch_pf_kind(dz_ctx *ctx, const DzStreamArgs &args, const DzDeltaPt
         a.S = ctx->force_splits;
         a.max_slots = 0;
     } else if (cus >= 8 && tiles % cus != 0) {
-        const int whole = (tiles / cus) * cus, tail = tiles - whole;
-        int S = cus / tail;
-        if (S > 4) S = 4;
+        const int whole = (tiles / cus) * cus, tail = (tiles - whole + 7) / 8 * 8;
+        const int S = std::min({cus / tail, 16, a.K / 512});
         if (S > 1) { a.S = S; a.max_slots = whole / 8; }
     }
     if (a.S > a.K / 256) a.S = a.K / 256;
@@ -579,35 +613,36 @@ hipError_t launch_pf_kind(dz_ctx *ctx, const DzStreamArgs &args, const DzDeltaPt
     a.partial = ctx->partial;
     a.counters = ctx->counters;
     if (a.has_delta && a.quant_only) {
-        if (a.has_base) return launch_pf_fmt<true, PW, PR, PJ, true, true>(a, dp, NRB, nchunks, L, st);
-        return launch_pf_fmt<true, PW, PR, PJ, false, true>(a, dp, NRB, nchunks, L, st);
+        if (a.has_base) return launch_pf_fmt<true, PW, PR, PJ, true, true>(a, gp, dp, NRB, nchunks, st);
+        return launch_pf_fmt<true, PW, PR, PJ, false, true>(a, gp, dp, NRB, nchunks, st);
     }
-    if (a.has_base && a.has_delta) return launch_pf_fmt<false, PW, PR, PJ, true, true>(a, dp, NRB, nchunks, L, st);
-    if (a.has_base) return launch_pf_fmt<false, PW, PR, PJ, true, false>(a, dp, NRB, nchunks, L, st);
-    return launch_pf_fmt<false, PW, PR, PJ, false, true>(a, dp, NRB, nchunks, L, st);
+    if (a.has_base && a.has_delta) return launch_pf_fmt<false, PW, PR, PJ, true, true>(a, gp, dp, NRB, nchunks, st);
+    if (a.has_base) return launch_pf_fmt<false, PW, PR, PJ, true, false>(a, gp, dp, NRB, nchunks, st);
+    return launch_pf_fmt<false, PW, PR, PJ, false, true>(a, gp, dp, NRB, nchunks, st);
 }
 
 }  // namespace
 
-int dz_launch_prefill(dz_ctx *ctx, const DzStreamArgs &args, const DzDeltaPtrs &dp, hipStream_t st)
+int dz_launch_prefill(dz_ctx *ctx, const DzStreamArgs &args, const DzGroup &gp, const DzGroupPtrs &dp, hipStream_t st)
 {
     DzStreamArgs a = args;
-    if ((unsigned long long)a.N * a.K * 2ull >= (1ull << 32)) return DZ_ERR_SHAPE;     // 32-bit byte offsets
+    for (int p = 0; p < gp.P; ++p)
+        if ((unsigned long long)gp.N[p] * a.K * 2ull >= (1ull << 32)) return DZ_ERR_SHAPE;     // 32-bit byte offsets
     if ((unsigned long long)a.T * a.K * 2ull >= (1ull << 31)) return DZ_ERR_SHAPE;     // x offsets, bit 31 = no row
     // The base product alone goes to the 256 x 256 tile kernel when that leaves enough tiles to keep
-    // enough CUs busy (measured: faster from about 0.3 tiles per CU on, slower below); DZ_TILE=2 sends
-    // every such call there, DZ_TILE=0 none.
-    if (ctx->tile_kernel && dz_tile_fits(a)) {
-        const long long wide_tiles = (long long)((a.N + 255) / 256) * ((a.T + 255) / 256);
-        const int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
-        if (ctx->tile_kernel > 1 || wide_tiles * 10 >= (long long)cus * 3) return dz_launch_tile(ctx, a, st);
+    // enough CUs busy (measured: faster from about 0.3 tiles per CU on, slower below); DZ_OPT_WIDE_TILE = 2
+    // sends every such call there, 0 none.
+    if (gp.P == 1) {
+        a.N = gp.N[0]; a.W = gp.W[0]; a.out = gp.out[0];
+        if (ctx->tile_kernel && dz_tile_fits(a)) {
+            const long long wide_tiles = (long long)((a.N + 255) / 256) * ((a.T + 255) / 256);
+            const int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
+            if (ctx->tile_kernel > 1 || wide_tiles * 10 >= (long long)cus * 3) return dz_launch_tile(ctx, a, st);
+        }
     }
-    DzLayout L = (a.has_delta && a.quant_only) ? dz_make_qlayout(a.N, a.K, a.bits, a.group)
-                                               : dz_make_layout(a.N, a.K, a.has_delta ? a.bits : 4, a.has_delta ? a.group : 128);
-    hipError_t e;
     int rc = DZ_OK;
     // 8 waves x 2 row tiles measured faster than 4 x 4 (two waves per SIMD hide each other's waits)
-    e = launch_pf_kind<8, 2, 8>(ctx, a, dp, L, st, &rc);
+    const hipError_t e = launch_pf_kind<8, 2, 8>(ctx, a, gp, dp, st, &rc);
     if (rc != DZ_OK) return rc;
     return dz_set_hip_error(ctx, e);
 }

@@ -165,7 +165,7 @@ __global__ __launch_bounds__(TTHREADS) void tile_kernel(DzStreamArgs a, int NRB,
 
     // ---- k slices of one tile meet in fp32 (as in the narrower tiled kernel): every slice stores
     // its accumulators with agent-scope stores, waits for them and bumps the tile's arrival
-    // counter; the last one adds the slices in slice order, its own from registers.
+    // counter; the last one adds all slices in slice order, 16 loads of each lane in flight at once.
     if (S > 1) {
         constexpr int AGENT = 0x10;
         const uint32_t tile_bytes = (uint32_t)(TRT * TJ) * TTHREADS * 16u;
@@ -192,18 +192,25 @@ __global__ __launch_bounds__(TTHREADS) void tile_kernel(DzStreamArgs a, int NRB,
 #pragma unroll
         for (int r = 0; r < TRT; ++r)
 #pragma unroll
-            for (int j = 0; j < TJ; ++j) {
-                f4 sum = (f4){0.f, 0.f, 0.f, 0.f};
-                for (int sl2 = 0; sl2 < S; ++sl2) {
-                    f4 v = acc[r][j];
-                    if (sl2 != ks)
-                        v = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                       prs, lane_off + (uint32_t)(r * TJ + j) * TTHREADS * 16u,
-                                                       (uint32_t)(slot0 + sl2) * tile_bytes, AGENT));
-                    sum += v;
-                }
-                acc[r][j] = sum;
+            for (int j = 0; j < TJ; ++j) acc[r][j] = (f4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int sl = 0; sl < S; ++sl) {
+#pragma unroll
+            for (int h = 0; h < TRT; h += 2) {
+                f4 v[2][TJ];
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j)
+                        v[r][j] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                             prs, lane_off + (uint32_t)((h + r) * TJ + j) * TTHREADS * 16u,
+                                                             (uint32_t)(slot0 + sl) * tile_bytes, AGENT));
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j) acc[h + r][j] += v[r][j];
             }
+        }
     }
     // ---- results: lane 16q + c holds rows 4q..4q+3 of each row tile for request column c
     _Float16 *out = (_Float16 *)a.out;

@@ -89,8 +89,8 @@ int dz_destroy(dz_ctx *ctx);
 #define DZ_OPT_WORKGROUPS            2  /* workgroups per launch of the streaming kernel; 0 = eight waves per compute unit            */
 #define DZ_OPT_ROUND_TILES           3  /* k tiles of x a workgroup of the streaming kernel stages at once; 0 = as many as fit        */
 #define DZ_OPT_LARGE_BATCH_STREAMING 4  /* 1 = batches of more than 64 rows also go through the streaming kernel, 64 rows at a time  */
-#define DZ_OPT_WIDE_TILE             5  /* dz_base_gemm on large batches: 0 = never the 256 x 256 tile kernel, 1 = when it has enough
-                                           tiles (default), 2 = always                                                                */
+#define DZ_OPT_WIDE_TILE             5  /* dz_base_gemm on more than 64 rows: 0 = never the wide tile kernel, 1 = where it is the faster
+                                           (default: everywhere it can run), 2 = everywhere it can run                                */
 #define DZ_OPT_REUSE_SEGMENTS        6  /* 1 = the caller promises that a token_to_delta vector passed again at the same address
                                            with the same T and D is unchanged: consecutive large-batch calls of one layer then share
                                            one sort.  Setting the option (to either value) forgets the remembered order.             */

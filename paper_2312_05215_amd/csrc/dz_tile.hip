@@ -7,7 +7,9 @@
 // large as the registers allow and both operands travel the cheapest way:
 //   * a workgroup (8 waves, 4 x 2) owns 256 rows of N x 256 request rows and walks k in steps of
 //     64; a wave owns 4 row tiles x 8 column blocks = 32 accumulator tiles (128 registers), the
-//     squarest wave tile, which needs the fewest fragment bytes from LDS per MFMA;
+//     squarest wave tile, which needs the fewest fragment bytes from LDS per MFMA.  Tiles of 5 to 7
+//     column blocks a wave, or of 5 to 7 row tiles with the waves as 2 x 4, are chosen where they fill
+//     the last round of one tile per CU better;
 //   * the W and x slices of a step go from global memory straight into LDS (buffer loads with an
 //     LDS destination: no staging registers, no LDS store instructions), double buffered, one
 //     barrier per step.  Such a load writes the 64 lanes' 16-byte pieces side by side, so LDS rows
@@ -21,22 +23,30 @@
 // Fused and delta-only calls stay with the narrower kernel: with 128 registers of accumulators the
 // packed-delta operands of a wave no longer fit beside them.
 #include "dz_mma.h"
+#include <algorithm>
 
 
 namespace {
 
 constexpr int TLD = 64;             // LDS row stride in halfs of a 64-k slice (no padding: see the swizzle)
-constexpr int TWR = 4, TWC = 2;     // waves along the rows of N and along the request rows
-constexpr int TW = TWR * TWC;       // 8 waves
-constexpr int TRT = 4;              // row tiles per wave
-constexpr int TJ = 8;               // column blocks per wave
-constexpr int TROWS = TWR * TRT * 16;   // 256 rows of N per tile
-constexpr int TCH = TWC * TJ * 16;      // 256 request rows per tile
+constexpr int TW = 8;               // waves per workgroup
 constexpr int TTHREADS = TW * 64;
 
+// 16 bytes per lane from global memory to LDS: 1 KB side by side, in lane order
+__device__ __forceinline__ void to_lds(__amdgpu_buffer_rsrc_t rs, _Float16 *lds, uint32_t voff, uint32_t soff)
+{
+    typedef __attribute__((address_space(3))) void lds_void;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)lds, 16, voff, soff, 0, 0);
+}
+
+// TWR x (8 / TWR) waves along the rows of N and along the request rows, each with TRT row tiles x TJ column blocks
+template <int TWR, int TRT, int TJ>
 __global__ __launch_bounds__(TTHREADS) void tile_kernel(DzStreamArgs a, int NRB, int nchunks)
 {
-    extern __shared__ __attribute__((aligned(16))) _Float16 lds[];     // W: 2 x [256][TLD]; x: 2 x [256][TLD]
+    constexpr int TWC = TW / TWR;
+    constexpr int TROWS = TWR * TRT * 16;   // rows of N per tile
+    constexpr int TCH = TWC * TJ * 16;      // request rows per tile
+    extern __shared__ __attribute__((aligned(16))) _Float16 lds[];     // W: 2 x [TROWS][TLD]; x: 2 x [TCH][TLD]
     _Float16 *const ws = lds;
     _Float16 *const xs = lds + 2 * TROWS * TLD;
     __shared__ int s_last;
@@ -94,24 +104,27 @@ __global__ __launch_bounds__(TTHREADS) void tile_kernel(DzStreamArgs a, int NRB,
     // zeros; whatever lands in LDS for them only reaches output rows that are never stored).
     const __amdgpu_buffer_rsrc_t rw = make_rsrc(a.W, (uint32_t)a.N * (uint32_t)a.K * 2u);
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(a.x, (uint32_t)a.T * (uint32_t)a.K * 2u);
-    uint32_t woff[4], xoff[4];
+    constexpr int WU = (TROWS + 63) / 64, XU = (TCH + 63) / 64;      // pieces per thread
+    uint32_t woff[WU], xoff[XU];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int r = u * 64 + (tid >> 3);
-        const uint32_t c = (uint32_t)((tid & 7) ^ ((r >> 1) & 7)) * 16u;
-        const int n = rb * TROWS + r, t = p0 + r;
-        woff[u] = n < a.N ? (uint32_t)n * (uint32_t)a.K * 2u + c : 0x80000000u;
-        xoff[u] = t < a.T ? (uint32_t)t * (uint32_t)a.K * 2u + c : 0x80000000u;
+    for (int u = 0; u < WU; ++u) {
+        const int r = u * 64 + (tid >> 3), n = rb * TROWS + r;
+        woff[u] = n < a.N ? (uint32_t)n * (uint32_t)a.K * 2u + (uint32_t)((tid & 7) ^ ((r >> 1) & 7)) * 16u : 0x80000000u;
     }
-    typedef __attribute__((address_space(3))) void lds_void;
+#pragma unroll
+    for (int u = 0; u < XU; ++u) {
+        const int r = u * 64 + (tid >> 3), t = p0 + r;
+        xoff[u] = t < a.T ? (uint32_t)t * (uint32_t)a.K * 2u + (uint32_t)((tid & 7) ^ ((r >> 1) & 7)) * 16u : 0x80000000u;
+    }
 #define TK_LOAD(buf, step)                                                                                         \
     do {                                                                                                           \
-        _Pragma("unroll") for (int u = 0; u < 4; ++u) {                                                           \
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void *)(ws + (buf) * TROWS * TLD + (u * 64 + wave * 8) * TLD), \
-                                                     16, woff[u], (uint32_t)(step) * 128u, 0, 0);                  \
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(xs + (buf) * TCH * TLD + (u * 64 + wave * 8) * TLD),   \
-                                                     16, xoff[u], (uint32_t)(step) * 128u, 0, 0);                  \
-        }                                                                                                          \
+        /* (a slice whose rows are no multiple of 64 ends before the last pieces of the later waves) */            \
+        _Pragma("unroll") for (int u = 0; u < WU; ++u)                                                            \
+            if (u * 64 + 64 <= TROWS || u * 64 + wave * 8 < TROWS)                                                 \
+                to_lds(rw, ws + (buf) * TROWS * TLD + (u * 64 + wave * 8) * TLD, woff[u], (uint32_t)(step) * 128u); \
+        _Pragma("unroll") for (int u = 0; u < XU; ++u)                                                            \
+            if (u * 64 + 64 <= TCH || u * 64 + wave * 8 < TCH)                                                     \
+                to_lds(rx, xs + (buf) * TCH * TLD + (u * 64 + wave * 8) * TLD, xoff[u], (uint32_t)(step) * 128u); \
     } while (0)
 
     const int s_first = 4 * kb, s_final = 4 * ke - 1;
@@ -124,6 +137,9 @@ __global__ __launch_bounds__(TTHREADS) void tile_kernel(DzStreamArgs a, int NRB,
     // One step: wait for the slice, request the next one into the other buffer, multiply.  A
     // workgroup walks a multiple of four steps, so the loop is unrolled by two and the buffer of a
     // step is known at compile time (all LDS addresses become immediates).
+    // A wave holds the fragments of the operand of which it has fewer, and streams the other's.
+    constexpr bool HOLD_A = TRT <= TJ;
+    constexpr int NH = HOLD_A ? TRT : TJ, NM = HOLD_A ? TJ : TRT;
 #define TK_STEP(BUF, step)                                                                                         \
     do {                                                                                                           \
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  /* this wave's pieces of slice `step` are in LDS */      \
@@ -132,25 +148,26 @@ __global__ __launch_bounds__(TTHREADS) void tile_kernel(DzStreamArgs a, int NRB,
         __builtin_amdgcn_sched_barrier(0);                                                                         \
         const _Float16 *wb = ws + (BUF) * TROWS * TLD;                                                             \
         const _Float16 *xb = xs + (BUF) * TCH * TLD;                                                               \
-        h8 af[TRT][2];                                                                                             \
-        _Pragma("unroll") for (int r = 0; r < TRT; ++r) {                                                         \
-            af[r][0] = *(const h8 *)(wb + aoff + r * 16 * TLD + f0);                                               \
-            af[r][1] = *(const h8 *)(wb + aoff + r * 16 * TLD + f1);                                               \
+        const _Float16 *hb = HOLD_A ? wb + aoff : xb + boff, *mb = HOLD_A ? xb + boff : wb + aoff;                 \
+        h8 hf[NH][2], mq[2][2];                                                                                    \
+        _Pragma("unroll") for (int i = 0; i < NH; ++i) {                                                          \
+            hf[i][0] = *(const h8 *)(hb + i * 16 * TLD + f0);                                                      \
+            hf[i][1] = *(const h8 *)(hb + i * 16 * TLD + f1);                                                      \
         }                                                                                                          \
-        h8 bq[2][2];                                                                                               \
-        bq[0][0] = *(const h8 *)(xb + boff + f0);                                                                  \
-        bq[0][1] = *(const h8 *)(xb + boff + f1);                                                                  \
-        bq[1][0] = *(const h8 *)(xb + boff + 16 * TLD + f0);                                                       \
-        bq[1][1] = *(const h8 *)(xb + boff + 16 * TLD + f1);                                                       \
-        _Pragma("unroll") for (int j = 0; j < TJ; ++j) {                                                          \
-            const h8 b0 = bq[j & 1][0], b1 = bq[j & 1][1];                                                         \
-            if (j + 2 < TJ) {                                                                                      \
-                bq[j & 1][0] = *(const h8 *)(xb + boff + (j + 2) * 16 * TLD + f0);                                 \
-                bq[j & 1][1] = *(const h8 *)(xb + boff + (j + 2) * 16 * TLD + f1);                                 \
+        mq[0][0] = *(const h8 *)(mb + f0);                                                                         \
+        mq[0][1] = *(const h8 *)(mb + f1);                                                                         \
+        mq[1][0] = *(const h8 *)(mb + 16 * TLD + f0);                                                              \
+        mq[1][1] = *(const h8 *)(mb + 16 * TLD + f1);                                                              \
+        _Pragma("unroll") for (int m = 0; m < NM; ++m) {                                                          \
+            const h8 m0 = mq[m & 1][0], m1 = mq[m & 1][1];                                                         \
+            if (m + 2 < NM) {                                                                                      \
+                mq[m & 1][0] = *(const h8 *)(mb + (m + 2) * 16 * TLD + f0);                                        \
+                mq[m & 1][1] = *(const h8 *)(mb + (m + 2) * 16 * TLD + f1);                                        \
             }                                                                                                      \
-            _Pragma("unroll") for (int r = 0; r < TRT; ++r) {                                                     \
-                acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[r][0], b0, acc[r][j], 0, 0, 0);              \
-                acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[r][1], b1, acc[r][j], 0, 0, 0);              \
+            _Pragma("unroll") for (int i = 0; i < NH; ++i) {                                                      \
+                f4 &c = acc[HOLD_A ? i : m][HOLD_A ? m : i];                                                       \
+                c = __builtin_amdgcn_mfma_f32_16x16x32_f16(HOLD_A ? hf[i][0] : m0, HOLD_A ? m0 : hf[i][0], c, 0, 0, 0); \
+                c = __builtin_amdgcn_mfma_f32_16x16x32_f16(HOLD_A ? hf[i][1] : m1, HOLD_A ? m1 : hf[i][1], c, 0, 0, 0); \
             }                                                                                                      \
             __builtin_amdgcn_sched_barrier(0);   /* keep the reads two blocks ahead of their MFMAs */               \
         }                                                                                                          \
@@ -193,22 +210,21 @@ __global__ __launch_bounds__(TTHREADS) void tile_kernel(DzStreamArgs a, int NRB,
         for (int r = 0; r < TRT; ++r)
 #pragma unroll
             for (int j = 0; j < TJ; ++j) acc[r][j] = (f4){0.f, 0.f, 0.f, 0.f};
+        constexpr int NV = TRT * TJ, BATCH = 16;
 #pragma unroll 1
         for (int sl = 0; sl < S; ++sl) {
 #pragma unroll
-            for (int h = 0; h < TRT; h += 2) {
-                f4 v[2][TJ];
+            for (int h = 0; h < NV; h += BATCH) {
+                f4 v[BATCH];
 #pragma unroll
-                for (int r = 0; r < 2; ++r)
+                for (int u = 0; u < BATCH; ++u)
+                    if (h + u < NV)
+                        v[u] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                          prs, lane_off + (uint32_t)(h + u) * TTHREADS * 16u,
+                                                          (uint32_t)(slot0 + sl) * tile_bytes, AGENT));
 #pragma unroll
-                    for (int j = 0; j < TJ; ++j)
-                        v[r][j] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                             prs, lane_off + (uint32_t)((h + r) * TJ + j) * TTHREADS * 16u,
-                                                             (uint32_t)(slot0 + sl) * tile_bytes, AGENT));
-#pragma unroll
-                for (int r = 0; r < 2; ++r)
-#pragma unroll
-                    for (int j = 0; j < TJ; ++j) acc[h + r][j] += v[r][j];
+                for (int u = 0; u < BATCH; ++u)
+                    if (h + u < NV) acc[(h + u) / TJ][(h + u) % TJ] += v[u];
             }
         }
     }
@@ -225,16 +241,43 @@ __global__ __launch_bounds__(TTHREADS) void tile_kernel(DzStreamArgs a, int NRB,
     }
 }
 
+template <int TWR, int TRT, int TJ>
 hipError_t launch_tile(const DzStreamArgs &a, int NRB, int nchunks, hipStream_t st)
 {
-    const size_t lds = (size_t)(2 * TROWS + 2 * TCH) * TLD * sizeof(_Float16);
-    static unsigned long long lds_allowed = 0;
-    const hipError_t e = dz_allow_lds((const void *)tile_kernel, (int)lds, lds_allowed);
+    const size_t lds = (size_t)2 * 16 * (TWR * TRT + TW / TWR * TJ) * TLD * sizeof(_Float16);
+    static unsigned long long lds_allowed = 0;      // per instantiation
+    const hipError_t e = dz_allow_lds((const void *)tile_kernel<TWR, TRT, TJ>, (int)lds, lds_allowed);
     if (e != hipSuccess) return e;
     const int tail = NRB * nchunks - 8 * a.max_slots;
     const int grid = 8 * (a.max_slots + ((tail + 7) / 8) * a.S);
-    hipLaunchKernelGGL(tile_kernel, dim3(grid), dim3(TTHREADS), lds, st, a, NRB, nchunks);
+    hipLaunchKernelGGL((tile_kernel<TWR, TRT, TJ>), dim3(grid), dim3(TTHREADS), lds, st, a, NRB, nchunks);
     return hipGetLastError();
+}
+
+// The tile shapes: 256 x 256 and the ones that are smaller in one direction.
+struct TileShape {
+    int twr, trt, tj;
+    int rows() const { return twr * trt * 16; }
+    int cols() const { return TW / twr * tj * 16; }
+};
+const TileShape shapes[] = {{4, 4, 8}, {4, 4, 7}, {4, 4, 6}, {4, 4, 5}, {4, 4, 4}, {2, 7, 4}, {2, 6, 4}, {2, 5, 4}};
+
+hipError_t launch_shape(const TileShape &t, const DzStreamArgs &a, int NRB, int nchunks, hipStream_t st)
+{
+    if (t.twr == 4) {
+        switch (t.tj) {
+        case 8: return launch_tile<4, 4, 8>(a, NRB, nchunks, st);
+        case 7: return launch_tile<4, 4, 7>(a, NRB, nchunks, st);
+        case 6: return launch_tile<4, 4, 6>(a, NRB, nchunks, st);
+        case 5: return launch_tile<4, 4, 5>(a, NRB, nchunks, st);
+        default: return launch_tile<4, 4, 4>(a, NRB, nchunks, st);
+        }
+    }
+    switch (t.trt) {
+    case 7: return launch_tile<2, 7, 4>(a, NRB, nchunks, st);
+    case 6: return launch_tile<2, 6, 4>(a, NRB, nchunks, st);
+    default: return launch_tile<2, 5, 4>(a, NRB, nchunks, st);
+    }
 }
 
 }  // namespace
@@ -251,26 +294,44 @@ int dz_launch_tile(dz_ctx *ctx, const DzStreamArgs &args, hipStream_t st)
 {
     DzStreamArgs a = args;
     if (!dz_tile_fits(a)) return DZ_ERR_SHAPE;
-    const int nchunks = (a.T + TCH - 1) / TCH;
-    const int NRB = (a.N + TROWS - 1) / TROWS;
-    // one workgroup per CU: the tiles of the full rounds run whole, those of the last, partly
-    // filled round are cut into up to four slices of k, as many as still fit the CUs at once
-    const int tiles = NRB * nchunks;
     int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
     cus -= cus % 8;
-    a.S = 1;
-    a.max_slots = (tiles + 7) / 8;
-    if (ctx->force_splits > 0) {
-        a.S = ctx->force_splits;
-        a.max_slots = 0;
-    } else if (cus >= 8 && tiles % cus != 0) {
-        const int whole = (tiles / cus) * cus, tail = tiles - whole;
-        int S = cus / tail;
-        if (S > 4) S = 4;
-        if (S > 1) { a.S = S; a.max_slots = whole / 8; }
+    // One workgroup per CU: the tiles of the full rounds run whole, those of the last, partly filled round are cut
+    // into up to eight slices of k, of two k tiles at least, as many as still fit the CUs at once.  Of the shapes the call takes the one with
+    // the least estimated time.  The estimate is in us, from measurements on a full chip: a step takes 0.75 + 0.87
+    // times the tile's area in units of 256 x 256 (1.61 for 256 x 256, 1.51 for 224 x 256, 1.30 for 160 x 256), a
+    // round some 6 more for its start and end, and a meeting moves the partial tiles of all slices twice.
+    // With slices of the smaller shapes even one tile fills the chip: 128 x 1024 x 8192 39.9 us in slices of the
+    // narrower kernel, 29.8 here.  T = 2048: 5120 x 5120 139 us with 256 x 256 tiles (160 for 256 CUs), 107 with 160 x 256 (256); 13824 x 5120
+    // 272 us with 256 x 256 (432: the second round is 69 % full), 257 with 224 x 256 (496).
+    const TileShape *best = nullptr;
+    double best_cost = 0;
+    int NRB = 0, nchunks = 0;
+    for (const TileShape &t : shapes) {
+        const int rb = (a.N + t.rows() - 1) / t.rows(), ch = (a.T + t.cols() - 1) / t.cols();
+        const long long tiles = (long long)rb * ch;
+        if (tiles > 0x3fffffff) continue;
+        int S = 1;
+        long long whole = tiles;
+        if (ctx->force_splits > 0) {
+            S = ctx->force_splits; whole = 0;
+        } else if (cus >= 8 && tiles % cus != 0) {
+            const int tail = (int)(tiles % cus);
+            const int fit = std::min({cus / tail, 8, a.K / 512});
+            if (fit > 1) { S = fit; whole = tiles - tail; }
+        }
+        const double area = t.rows() * t.cols() / 65536.0, step = 0.75 + 0.87 * area, n = cus > 0 ? cus : 256;
+        double cost = (double)((whole + (long long)n - 1) / (long long)n) * (step * (a.K / 64) + 6.0);
+        if (whole < tiles) cost += step * ((a.K / 64 + S - 1) / S) + 6.0 + 3.0 * S * area * ((double)(tiles - whole) * S / n);
+        if (!best || cost < best_cost) {
+            best = &t; best_cost = cost; NRB = rb; nchunks = ch;
+            a.S = S; a.max_slots = S > 1 ? (int)(whole / 8) : (int)((tiles + 7) / 8);
+        }
     }
+    if (!best) return DZ_ERR_SHAPE;
+    const int tiles = NRB * nchunks;
     if (a.S > a.K / 256) a.S = a.K / 256;
-    const size_t tile_bytes = (size_t)TRT * TJ * TTHREADS * 16;
+    const size_t tile_bytes = (size_t)best->trt * best->tj * TTHREADS * 16;
     const int sliced = 8 * ((tiles - 8 * a.max_slots + 7) / 8);
     if (a.S > 1 && (size_t)sliced * a.S * tile_bytes >= ((size_t)1 << 32)) a.S = 1;     // 32-bit byte offsets
     if (a.S <= 1) { a.S = 1; a.max_slots = (tiles + 7) / 8; }
@@ -281,5 +342,5 @@ int dz_launch_tile(dz_ctx *ctx, const DzStreamArgs &args, hipStream_t st)
     }
     a.partial = ctx->partial;
     a.counters = ctx->counters;
-    return dz_set_hip_error(ctx, launch_tile(a, NRB, nchunks, st));
+    return dz_set_hip_error(ctx, launch_shape(*best, a, NRB, nchunks, st));
 }

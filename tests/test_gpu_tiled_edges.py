@@ -39,3 +39,27 @@ def test_group_of_projections_in_one_tiled_launch(dz, group, idle):
                 want = oracle.c.linear(x.numpy(), cs.W.numpy(), cs.dense, idv.numpy())
                 assert_close(o[1:-1], want, f"N={cs.N}")
                 assert (o[0] == 7).all() and (o[-1] == 7).all()
+
+
+# sizes that take each tile shape of the base product in turn, whole and in slices of k, with ragged last tiles
+BASE = [(65, 16, 256), (65, 16, 1024), (128, 272, 4096), (130, 3088, 2048), (500, 11024, 1024), (1000, 6160, 1024),
+        (1000, 8208, 256), (1000, 11024, 256), (1500, 8208, 256), (1500, 11024, 2048), (2049, 272, 2048), (2049, 8208, 1024)]
+
+
+@pytest.mark.parametrize("T,N,K", BASE)
+def test_base_product_tile_shapes(dz, T, N, K):
+    """Against torch in fp32: half a unit of fp16 in the last place, 4.9e-4, and the order of the fp32 sums."""
+    print(f"case T={T} N={N} K={K}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(T + N + K)
+    x = torch.randn(T, K, generator=gen, device="cuda").half()
+    W = (torch.randn(N, K, generator=gen, device="cuda") * 0.02).half()
+    want = x.float() @ W.float().t()
+    buf = torch.full((T + 2, N), 7.0, dtype=torch.float16, device="cuda")
+    with dz.Context(0) as c:
+        for repeat in range(2):
+            buf[1:-1] = 7.0
+            dz.dz_base_gemm(c.h, x, W, buf[1:-1], T, N, K)
+            rms = want.pow(2).mean().sqrt()
+            off = ((buf[1:-1].float() - want).abs() / torch.maximum(want.abs(), rms)).max().item()
+            assert off < 1e-3, off
+            assert (buf[0] == 7).all() and (buf[-1] == 7).all()

@@ -304,29 +304,42 @@ int dz_launch_tile(dz_ctx *ctx, const DzStreamArgs &args, hipStream_t st)
     // With slices of the smaller shapes even one tile fills the chip: 128 x 1024 x 8192 39.9 us in slices of the
     // narrower kernel, 29.8 here.  T = 2048: 5120 x 5120 139 us with 256 x 256 tiles (160 for 256 CUs), 107 with 160 x 256 (256); 13824 x 5120
     // 272 us with 256 x 256 (432: the second round is 69 % full), 257 with 224 x 256 (496).
+    // The partial tiles of a call take up to 64 MB, twice what dz_create makes room for.  A call that is being captured
+    // into a graph without an eager call before it cannot grow the workspace: it takes the best split that fits.
+    size_t room = (size_t)64 << 20;
     const TileShape *best = nullptr;
     double best_cost = 0;
     int NRB = 0, nchunks = 0;
-    for (const TileShape &t : shapes) {
-        const int rb = (a.N + t.rows() - 1) / t.rows(), ch = (a.T + t.cols() - 1) / t.cols();
-        const long long tiles = (long long)rb * ch;
-        if (tiles > 0x3fffffff) continue;
-        int S = 1;
-        long long whole = tiles;
-        if (ctx->force_splits > 0) {
-            S = ctx->force_splits; whole = 0;
-        } else if (cus >= 8 && tiles % cus != 0) {
-            const int tail = (int)(tiles % cus);
-            const int fit = std::min({cus / tail, 8, a.K / 512});
-            if (fit > 1) { S = fit; whole = tiles - tail; }
+    auto choose = [&]() {
+        best = nullptr;
+        for (const TileShape &t : shapes) {
+            const int rb = (a.N + t.rows() - 1) / t.rows(), ch = (a.T + t.cols() - 1) / t.cols();
+            const long long tiles = (long long)rb * ch;
+            if (tiles > 0x3fffffff) continue;
+            int S = 1;
+            long long whole = tiles;
+            if (ctx->force_splits > 0) {
+                S = ctx->force_splits; whole = 0;
+            } else if (cus >= 8 && tiles % cus != 0) {
+                const int tail = (int)(tiles % cus), sliced = (tail + 7) / 8 * 8;       // (dealt out to the XCDs in eights)
+                const int fit = std::min({cus / sliced, 8, a.K / 512, (int)(room / ((size_t)sliced * t.trt * t.tj * TTHREADS * 16))});
+                if (fit > 1) { S = fit; whole = tiles - tail; }
+            }
+            const double area = t.rows() * t.cols() / 65536.0, step = 0.75 + 0.87 * area, n = cus > 0 ? cus : 256;
+            double cost = (double)((whole + (long long)n - 1) / (long long)n) * (step * (a.K / 64) + 6.0);
+            if (whole < tiles) cost += step * ((a.K / 64 + S - 1) / S) + 6.0 + 5.0 * S * area * ((double)(tiles - whole) * S / n);
+            if (!best || cost < best_cost) {
+                best = &t; best_cost = cost; NRB = rb; nchunks = ch;
+                a.S = S; a.max_slots = S > 1 ? (int)(whole / 8) : (int)((tiles + 7) / 8);
+            }
         }
-        const double area = t.rows() * t.cols() / 65536.0, step = 0.75 + 0.87 * area, n = cus > 0 ? cus : 256;
-        double cost = (double)((whole + (long long)n - 1) / (long long)n) * (step * (a.K / 64) + 6.0);
-        if (whole < tiles) cost += step * ((a.K / 64 + S - 1) / S) + 6.0 + 3.0 * S * area * ((double)(tiles - whole) * S / n);
-        if (!best || cost < best_cost) {
-            best = &t; best_cost = cost; NRB = rb; nchunks = ch;
-            a.S = S; a.max_slots = S > 1 ? (int)(whole / 8) : (int)((tiles + 7) / 8);
-        }
+    };
+    choose();
+    if (best && a.S > 1 && 8ull * ((NRB * (long long)nchunks - 8 * a.max_slots + 7) / 8) * a.S * best->trt * best->tj * TTHREADS * 16 > ctx->partial_bytes) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        const hipError_t e = hipStreamIsCapturing(st, &cs);
+        if (e != hipSuccess) return dz_set_hip_error(ctx, e);
+        if (cs != hipStreamCaptureStatusNone && ctx->force_splits == 0) { room = ctx->partial_bytes; choose(); }
     }
     if (!best) return DZ_ERR_SHAPE;
     const int tiles = NRB * nchunks;

@@ -127,3 +127,27 @@ def test_replay_after_the_workspace_grew(dz):
             torch.cuda.synchronize()
             assert dz.dz_check(c.h) == dz.DZ_OK
             assert_close(o, oracle.c.linear(xn.numpy(), small.W.numpy(), small.dense, small.ids.numpy()), f"replay {rep} after growth")
+
+
+@pytest.mark.parametrize("T,N,K", [(100, 1024, 8192), (300, 4096, 4096), (200, 11008, 4096)])
+def test_small_base_products_are_captured_cold(dz, T, N, K):
+    """The first call of a context can be a captured one: slices of k then fit the workspace as dz_create made it, also
+    where an eager call would grow it (the last size).  Several replays, with other work between them."""
+    print(f"cold capture T={T} N={N} K={K}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.randn(T, K, generator=gen, device="cuda").half()
+    W = (torch.randn(N, K, generator=gen, device="cuda") * 0.02).half()
+    out = torch.empty(T, N, dtype=torch.float16, device="cuda")
+    with dz.Context(0) as c:
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            dz.dz_base_gemm(c.h, x, W, out, T, N, K)
+        for rep in range(3):
+            x.copy_(torch.randn(T, K, generator=gen, device="cuda").half())
+            out.fill_(7.0)
+            graph.replay()
+            torch.cuda.synchronize()
+            want = x.float() @ W.float().t()
+            off = ((out.float() - want).abs() / torch.maximum(want.abs(), want.pow(2).mean().sqrt())).max().item()
+            assert off < 1e-3, (rep, off)        # half a unit of fp16 in the last place and the order of fp32 sums

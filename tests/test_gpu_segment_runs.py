@@ -1,0 +1,25 @@
+"""GPU: dz_segment where its runs of requests can go wrong: one wave's run, several, the last one short or empty, more
+keys than fit more than one histogram, every request the same key, all idle, indices out of range in a late run."""
+import numpy as np
+import pytest
+
+import dz_synth as S
+from test_gpu_segment import _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [1, 2, 63, 64, 127, 128, 1023, 4000, 8192])
+@pytest.mark.parametrize("T", [1, 63, 64, 65, 128, 1023, 1025, 3000])
+def test_runs(dz, T, D):
+    print(f"case T={T} D={D}", flush=True)
+    with dz.Context(0) as c:
+        ids = S.ids_uniform(T, D, S.stream(61, "r", T, D)).numpy().copy()
+        ids[::5] = -1
+        _run(dz, c, ids, D)
+        _run(dz, c, np.full(T, D - 1), D)
+        _run(dz, c, np.full(T, -1), D)
+        assert dz.dz_check(c.h) == dz.DZ_OK
+        ids[T - 1] = D
+        _run(dz, c, ids, D)
+        assert dz.dz_check(c.h) == dz.DZ_ERR_INDEX

@@ -79,6 +79,9 @@ def profile_traffic(kernel: str, workload: str, launches_per_layer: int):
             if ln.startswith("traffic_"):
                 k, v = ln.split(":")
                 prof[k] = int(v)
+        at = f"traffic_bytes_per_launch_at_{launches_per_layer}_per_layer"      # a second grouping in the same file
+        if at in prof:
+            return prof[at], os.path.relpath(path, ROOT)
         if prof.get("traffic_launches_per_layer") == launches_per_layer:
             return prof.get("traffic_bytes_per_launch"), os.path.relpath(path, ROOT)
     except (OSError, ValueError):
@@ -208,8 +211,8 @@ def run_workload(args, name, steps, warmup, with_cpu, primary):
     ms_model = ms_per_step * cfg.layers / n_layers
     tokens_per_s = cfg.T / (ms_model * 1e-3)
 
-    # kernel launches per layer: one per call for small batches; large batches run one tiled kernel per projection
-    launches_per_layer = len(groups) if (grouped and cfg.T <= 64) else len(projs)
+    # kernel launches per layer: one per call (the segment pass of large batches, one per layer, is not counted)
+    launches_per_layer = len(groups) if grouped else len(projs)
     launches_per_step = n_layers * launches_per_layer
     act = 0 if path == "base" else n_active
     bytes_per_step = n_layers * sum(S.algorithmic_bytes(N, K, cfg.T, cfg.bits, cfg.group, act) - (2 * N * K if path == "sbmm" else 0)

@@ -230,7 +230,7 @@ int dz_merge_delta(dz_ctx *ctx, const void *W_f16, const void *packed, int N, in
  *   out[p][t] = f16( x[t] . W[p]^T + x[t] . Delta[p][token_to_delta[t]]^T ),   p = 0 .. P-1,
  * each exactly what dz_linear computes for projection p alone.  The base and delta products of a
  * layer are independent per output feature (Section 5.1, Eq. (2)), so stacking projections along
- * the output dimension changes no result; for decode-sized batches (T <= 64) all P projections go
+ * the output dimension changes no result; all P projections go
  * through one kernel launch, which saves the fixed cost of P - 1 launches (Section 5.2 argues the
  * same way for batching all deltas of a layer into one launch).
  *   W, out          HOST arrays of P DEVICE pointers; N a HOST array of P output sizes

@@ -107,8 +107,8 @@ int dz_launch_segment(dz_ctx *, const int32_t *ids, int T, int D, int32_t *count
                       int32_t *perm, int32_t *key, hipStream_t);
 int dz_launch_stream(dz_ctx *, const DzStreamArgs &, const DzGroup &, const DzGroupPtrs &, hipStream_t);
 int dz_launch_prefill(dz_ctx *, const DzStreamArgs &, const DzGroup &, const DzGroupPtrs &, hipStream_t);
-int dz_launch_tile(dz_ctx *, const DzStreamArgs &, hipStream_t);
-bool dz_tile_fits(const DzStreamArgs &);
+int dz_launch_tile(dz_ctx *, const DzStreamArgs &, const DzGroup &, hipStream_t);
+bool dz_tile_fits(const DzStreamArgs &, const DzGroup &);
 int dz_launch_qpack(dz_ctx *, const uint8_t *codes, const void *scale, const void *zero, int N, int K, int bits, int group,
                     void *packed, hipStream_t);
 int dz_launch_qunpack(dz_ctx *, const void *packed, int N, int K, int bits, int group, uint8_t *codes, void *scale,

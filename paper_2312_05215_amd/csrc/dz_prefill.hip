@@ -625,21 +625,18 @@ hipError_t launch_pf_kind(dz_ctx *ctx, const DzStreamArgs &args, const DzGroup &
 
 int dz_launch_prefill(dz_ctx *ctx, const DzStreamArgs &args, const DzGroup &gp, const DzGroupPtrs &dp, hipStream_t st)
 {
-    DzStreamArgs a = args;
     for (int p = 0; p < gp.P; ++p)
-        if ((unsigned long long)gp.N[p] * a.K * 2ull >= (1ull << 32)) return DZ_ERR_SHAPE;     // 32-bit byte offsets
-    if ((unsigned long long)a.T * a.K * 2ull >= (1ull << 31)) return DZ_ERR_SHAPE;     // x offsets, bit 31 = no row
-    // The base product alone goes to the wide tile kernel, which has a tile shape for every batch of more than 64
-    // rows: on 56 sizes from 65 x 1024 x 1024 to 1000 x 28672 x 8192 it took 0.66 to 1.05 times as long as the
-    // kernel here (22.5 -> 15.7 us at 128 x 1024 x 1024, 34.4 -> 30.4 at 256 x 4096 x 4096, 549 -> 400 at the largest).
-    // What is left to this one are weights of 2 GiB and more, and calls with DZ_OPT_WIDE_TILE = 0.
-    if (gp.P == 1) {
-        a.N = gp.N[0]; a.W = gp.W[0]; a.out = gp.out[0];
-        if (ctx->tile_kernel && dz_tile_fits(a)) return dz_launch_tile(ctx, a, st);
-    }
+        if ((unsigned long long)gp.N[p] * args.K * 2ull >= (1ull << 32)) return DZ_ERR_SHAPE;     // 32-bit byte offsets
+    if ((unsigned long long)args.T * args.K * 2ull >= (1ull << 31)) return DZ_ERR_SHAPE;     // x offsets, bit 31 = no row
+    // Base products alone, one projection or several, go to the wide tile kernel, which has a tile shape for every batch
+    // of more than 64 rows: on 56 sizes of one projection from 65 x 1024 x 1024 to 1000 x 28672 x 8192 it took 0.66 to
+    // 1.05 times as long as the kernel here (22.5 -> 15.7 us at 128 x 1024 x 1024, 34.4 -> 30.4 at 256 x 4096 x 4096, 549
+    // -> 400 at the largest), on groups of projections 0.5 to 1.1 times.  What is left to this one are calls in which
+    // some weight has 2 GiB or more, and calls with DZ_OPT_WIDE_TILE = 0.
+    if (ctx->tile_kernel && dz_tile_fits(args, gp)) return dz_launch_tile(ctx, args, gp, st);
     int rc = DZ_OK;
     // 8 waves x 2 row tiles measured faster than 4 x 4 (two waves per SIMD hide each other's waits)
-    const hipError_t e = launch_pf_kind<8, 2, 8>(ctx, a, gp, dp, st, &rc);
+    const hipError_t e = launch_pf_kind<8, 2, 8>(ctx, args, gp, dp, st, &rc);
     if (rc != DZ_OK) return rc;
     return dz_set_hip_error(ctx, e);
 }

@@ -20,6 +20,11 @@
 //     blocks ahead of the MFMAs that use it;
 //   * the tiles of the last, partly filled round of one-tile-per-CU are cut into k slices that
 //     meet in fp32, as in the narrower tiled kernel.
+//   * the projections of one call are one launch, their row blocks numbered one projection after the other:
+//     dz_linear_group without deltas, us in one launch of the narrower kernel -> here: 65 x (3 x 1024) x 1024 20.5 ->
+//     15.2, 777 x (3 x 4096) x 4096 116 -> 74 (154 with a launch here for each), 2048 x (2 x 11008) x 4096 455 -> 346,
+//     1000 x (2 x 28672) x 8192 1089 -> 815; 0.5 to 1.1 times as long over 310 sizes of two to four projections, the
+//     1.1 where a batch of up to 256 rows just fills the narrower kernel's last round.
 // Fused and delta-only calls stay with the narrower kernel: with 128 registers of accumulators the
 // packed-delta operands of a wave no longer fit beside them.
 #include "dz_mma.h"
@@ -40,8 +45,8 @@ __device__ __forceinline__ void to_lds(__amdgpu_buffer_rsrc_t rs, _Float16 *lds,
 }
 
 // TWR x (8 / TWR) waves along the rows of N and along the request rows, each with TRT row tiles x TJ column blocks
-template <int TWR, int TRT, int TJ>
-__global__ __launch_bounds__(TTHREADS) void tile_kernel(DzStreamArgs a, int NRB, int nchunks)
+template <int TWR, int TRT, int TJ, bool GROUP>
+__global__ __launch_bounds__(TTHREADS) void tile_kernel(DzStreamArgs a, DzGroup gp, int NRB, int nchunks)
 {
     constexpr int TWC = TW / TWR;
     constexpr int TROWS = TWR * TRT * 16;   // rows of N per tile
@@ -81,13 +86,22 @@ __global__ __launch_bounds__(TTHREADS) void tile_kernel(DzStreamArgs a, int NRB,
     const int kb = (int)((uint32_t)ks * (uint32_t)g.KT / (uint32_t)S);      // k tiles [kb, ke)
     const int ke = (int)((uint32_t)(ks + 1) * (uint32_t)g.KT / (uint32_t)S);
     const int p0 = chunk * TCH;
-    const int RT = a.N >> 4;
+    // The projection this row block belongs to: their row blocks are numbered one after the other.  A call of one projection
+    // has a kernel of its own, since looking the projection up makes the start 0.4 us longer (15.2 -> 15.6 us at
+    // 256 x 1024 x 1024).
+    int pj = 0;
+    if constexpr (GROUP) {
+        while (pj + 1 < gp.P && rb >= gp.rb_start[pj + 1]) ++pj;
+    }
+    const int rbl = GROUP ? rb - gp.rb_start[pj] : rb;
+    const int Np = GROUP ? gp.N[pj] : a.N;
+    const int RT = Np >> 4;
 
     int rtc[TRT];
     bool rvalid[TRT];
 #pragma unroll
     for (int r = 0; r < TRT; ++r) {
-        const int rt = rb * (TWR * TRT) + wr * TRT + r;
+        const int rt = rbl * (TWR * TRT) + wr * TRT + r;
         rvalid[r] = rt < RT;
         rtc[r] = rvalid[r] ? rt : RT - 1;
     }
@@ -102,14 +116,14 @@ __global__ __launch_bounds__(TTHREADS) void tile_kernel(DzStreamArgs a, int NRB,
     // lanes cover 8 consecutive rows = 1 KB of LDS in lane order, as the LDS-destination load
     // writes it.  Rows that do not exist get an offset beyond the resource (the hardware reads
     // zeros; whatever lands in LDS for them only reaches output rows that are never stored).
-    const __amdgpu_buffer_rsrc_t rw = make_rsrc(a.W, (uint32_t)a.N * (uint32_t)a.K * 2u);
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(GROUP ? gp.W[pj] : a.W, (uint32_t)Np * (uint32_t)a.K * 2u);
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(a.x, (uint32_t)a.T * (uint32_t)a.K * 2u);
     constexpr int WU = (TROWS + 63) / 64, XU = (TCH + 63) / 64;      // pieces per thread
     uint32_t woff[WU], xoff[XU];
 #pragma unroll
     for (int u = 0; u < WU; ++u) {
-        const int r = u * 64 + (tid >> 3), n = rb * TROWS + r;
-        woff[u] = n < a.N ? (uint32_t)n * (uint32_t)a.K * 2u + (uint32_t)((tid & 7) ^ ((r >> 1) & 7)) * 16u : 0x80000000u;
+        const int r = u * 64 + (tid >> 3), n = rbl * TROWS + r;
+        woff[u] = n < Np ? (uint32_t)n * (uint32_t)a.K * 2u + (uint32_t)((tid & 7) ^ ((r >> 1) & 7)) * 16u : 0x80000000u;
     }
 #pragma unroll
     for (int u = 0; u < XU; ++u) {
@@ -229,28 +243,29 @@ __global__ __launch_bounds__(TTHREADS) void tile_kernel(DzStreamArgs a, int NRB,
         }
     }
     // ---- results: lane 16q + c holds rows 4q..4q+3 of each row tile for request column c
-    _Float16 *out = (_Float16 *)a.out;
+    _Float16 *out = (_Float16 *)(GROUP ? gp.out[pj] : a.out);
 #pragma unroll
     for (int r = 0; r < TRT; ++r) {
         if (!rvalid[r]) continue;
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
             const int tok = p0 + (wc * TJ + j) * 16 + g.row;
-            if (tok < a.T) store_row4(out + (size_t)tok * a.N + rtc[r] * 16 + 4 * g.q, acc[r][j], a.accumulate);
+            if (tok < a.T) store_row4(out + (size_t)tok * Np + rtc[r] * 16 + 4 * g.q, acc[r][j], a.accumulate);
         }
     }
 }
 
-template <int TWR, int TRT, int TJ>
-hipError_t launch_tile(const DzStreamArgs &a, int NRB, int nchunks, hipStream_t st)
+template <int TWR, int TRT, int TJ, bool GROUP>
+hipError_t launch_tile(const DzStreamArgs &a, const DzGroup &gp, int NRB, int nchunks, hipStream_t st)
 {
     const size_t lds = (size_t)2 * 16 * (TWR * TRT + TW / TWR * TJ) * TLD * sizeof(_Float16);
     static unsigned long long lds_allowed = 0;      // per instantiation
-    const hipError_t e = dz_allow_lds((const void *)tile_kernel<TWR, TRT, TJ>, (int)lds, lds_allowed);
+    auto k = tile_kernel<TWR, TRT, TJ, GROUP>;
+    const hipError_t e = dz_allow_lds((const void *)k, (int)lds, lds_allowed);
     if (e != hipSuccess) return e;
     const int tail = NRB * nchunks - 8 * a.max_slots;
     const int grid = 8 * (a.max_slots + ((tail + 7) / 8) * a.S);
-    hipLaunchKernelGGL((tile_kernel<TWR, TRT, TJ>), dim3(grid), dim3(TTHREADS), lds, st, a, NRB, nchunks);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(TTHREADS), lds, st, a, gp, NRB, nchunks);
     return hipGetLastError();
 }
 
@@ -262,38 +277,42 @@ struct TileShape {
 };
 const TileShape shapes[] = {{4, 4, 8}, {4, 4, 7}, {4, 4, 6}, {4, 4, 5}, {4, 4, 4}, {2, 7, 4}, {2, 6, 4}, {2, 5, 4}};
 
-hipError_t launch_shape(const TileShape &t, const DzStreamArgs &a, int NRB, int nchunks, hipStream_t st)
+template <bool GROUP>
+hipError_t launch_shape(const TileShape &t, const DzStreamArgs &a, const DzGroup &gp, int NRB, int nchunks, hipStream_t st)
 {
     if (t.twr == 4) {
         switch (t.tj) {
-        case 8: return launch_tile<4, 4, 8>(a, NRB, nchunks, st);
-        case 7: return launch_tile<4, 4, 7>(a, NRB, nchunks, st);
-        case 6: return launch_tile<4, 4, 6>(a, NRB, nchunks, st);
-        case 5: return launch_tile<4, 4, 5>(a, NRB, nchunks, st);
-        default: return launch_tile<4, 4, 4>(a, NRB, nchunks, st);
+        case 8: return launch_tile<4, 4, 8, GROUP>(a, gp, NRB, nchunks, st);
+        case 7: return launch_tile<4, 4, 7, GROUP>(a, gp, NRB, nchunks, st);
+        case 6: return launch_tile<4, 4, 6, GROUP>(a, gp, NRB, nchunks, st);
+        case 5: return launch_tile<4, 4, 5, GROUP>(a, gp, NRB, nchunks, st);
+        default: return launch_tile<4, 4, 4, GROUP>(a, gp, NRB, nchunks, st);
         }
     }
     switch (t.trt) {
-    case 7: return launch_tile<2, 7, 4>(a, NRB, nchunks, st);
-    case 6: return launch_tile<2, 6, 4>(a, NRB, nchunks, st);
-    default: return launch_tile<2, 5, 4>(a, NRB, nchunks, st);
+    case 7: return launch_tile<2, 7, 4, GROUP>(a, gp, NRB, nchunks, st);
+    case 6: return launch_tile<2, 6, 4, GROUP>(a, gp, NRB, nchunks, st);
+    default: return launch_tile<2, 5, 4, GROUP>(a, gp, NRB, nchunks, st);
     }
 }
 
 }  // namespace
 
-// Does the wide kernel take this call?  Base product only, requests in their own order, and every
+// Does the wide kernel take this call?  Base products only, requests in their own order, and every
 // real byte offset below 2^31 (its missing-row trick uses the upper half of the offset range).
-bool dz_tile_fits(const DzStreamArgs &a)
+bool dz_tile_fits(const DzStreamArgs &a, const DzGroup &gp)
 {
     if (!a.has_base || a.has_delta || a.perm != nullptr) return false;
-    return (unsigned long long)a.N * a.K * 2ull < (1ull << 31) && (unsigned long long)a.T * a.K * 2ull < (1ull << 31);
+    for (int p = 0; p < gp.P; ++p)
+        if ((unsigned long long)gp.N[p] * a.K * 2ull >= (1ull << 31)) return false;
+    return (unsigned long long)a.T * a.K * 2ull < (1ull << 31);
 }
 
-int dz_launch_tile(dz_ctx *ctx, const DzStreamArgs &args, hipStream_t st)
+int dz_launch_tile(dz_ctx *ctx, const DzStreamArgs &args, const DzGroup &group, hipStream_t st)
 {
     DzStreamArgs a = args;
-    if (!dz_tile_fits(a)) return DZ_ERR_SHAPE;
+    DzGroup gp = group;
+    if (!dz_tile_fits(a, gp)) return DZ_ERR_SHAPE;
     int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
     cus -= cus % 8;
     // One workgroup per CU: the tiles of the full rounds run whole, those of the last, partly filled round are cut
@@ -313,7 +332,9 @@ int dz_launch_tile(dz_ctx *ctx, const DzStreamArgs &args, hipStream_t st)
     auto choose = [&]() {
         best = nullptr;
         for (const TileShape &t : shapes) {
-            const int rb = (a.N + t.rows() - 1) / t.rows(), ch = (a.T + t.cols() - 1) / t.cols();
+            int rb = 0;                     // row blocks of all projections; a row block never spans two
+            for (int p = 0; p < gp.P; ++p) rb += (gp.N[p] + t.rows() - 1) / t.rows();
+            const int ch = (a.T + t.cols() - 1) / t.cols();
             const long long tiles = (long long)rb * ch;
             if (tiles > 0x3fffffff) continue;
             int S = 1;
@@ -342,6 +363,9 @@ int dz_launch_tile(dz_ctx *ctx, const DzStreamArgs &args, hipStream_t st)
         if (cs != hipStreamCaptureStatusNone && ctx->force_splits == 0) { room = ctx->partial_bytes; choose(); }
     }
     if (!best) return DZ_ERR_SHAPE;
+    gp.rb_start[0] = 0;
+    for (int p = 0; p < DZ_MAX_GROUP; ++p)
+        gp.rb_start[p + 1] = gp.rb_start[p] + (p < gp.P ? (gp.N[p] + best->rows() - 1) / best->rows() : 0);
     const int tiles = NRB * nchunks;
     if (a.S > a.K / 256) a.S = a.K / 256;
     const size_t tile_bytes = (size_t)best->trt * best->tj * TTHREADS * 16;
@@ -355,5 +379,7 @@ int dz_launch_tile(dz_ctx *ctx, const DzStreamArgs &args, hipStream_t st)
     }
     a.partial = ctx->partial;
     a.counters = ctx->counters;
-    return dz_set_hip_error(ctx, launch_shape(*best, a, NRB, nchunks, st));
+    if (gp.P > 1) return dz_set_hip_error(ctx, launch_shape<true>(*best, a, gp, NRB, nchunks, st));
+    a.N = gp.N[0]; a.W = gp.W[0]; a.out = gp.out[0];
+    return dz_set_hip_error(ctx, launch_shape<false>(*best, a, gp, NRB, nchunks, st));
 }

@@ -10,12 +10,14 @@
 // walked all requests, and all distinct keys of each 64 in turn, a call took 122 us at T = 2048 over 16 deltas in
 // mixed order (17.5 us where every 64 name one or two), 54 us at T = 512 over 32; it takes 8 us from T = 65 to
 // 2048 (calls back to back, of which the launch is most) and 16 us at T = 8192 over 128, before 1480.
+// The prefix sum is shared by the waves too: one wave that walked all of it took 55 us for one request over 8192 keys
+// and 29 over 4096 (10 and 8 here), and 248 us at T = 8192 over 8192 (202 here).
 #include "dz_internal.h"
 
 namespace {
 
 constexpr int SEG_WAVES = 16, SEG_THREADS = SEG_WAVES * 64;
-constexpr int SEG_LDS = 64 * 1024;      // what a launch may ask for without an attribute
+constexpr int SEG_LDS = 64 * 1024 - SEG_WAVES * 4;      // what a launch may use without an attribute, less s_total
 
 __device__ inline unsigned lanes_below(unsigned long long m)
 {
@@ -47,6 +49,7 @@ __global__ __launch_bounds__(SEG_THREADS) void segment_kernel(const int32_t *__r
                                                               int32_t *__restrict__ err_flag)
 {
     extern __shared__ int32_t cursor[];          // [runs][D + 1] histograms, then running write cursors
+    __shared__ int32_t s_total[SEG_WAVES];       // requests of each wave's run of keys
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (int i = tid; i < runs * (D + 1); i += SEG_THREADS) cursor[i] = 0;
     __syncthreads();
@@ -62,32 +65,43 @@ __global__ __launch_bounds__(SEG_THREADS) void segment_kernel(const int32_t *__r
     }
     if (__ballot(bad) && lane == 0) atomicOr(err_flag, 1);
     __syncthreads();
-    // exclusive prefix sum over the D + 1 keys and the runs within a key, by wave 0: 64 keys per round, carried total in `base`
-    if (tid < 64) {
-        int base = 0;
-        for (int i0 = 0; i0 <= D; i0 += 64) {
-            const int i = i0 + tid;
-            int c = 0;
-            if (i <= D)
-                for (int w = 0; w < runs; ++w) c += cursor[w * (D + 1) + i];
-            int incl = c;
+    // Exclusive prefix sum over the D + 1 keys and the runs within a key.  Each wave owns a run of keys, 64 at a time, on
+    // top of the totals of the waves below it; where 64 keys are all, wave 0 has them and needs no totals.
+    const int keys = (D + 64 * SEG_WAVES) / (64 * SEG_WAVES) * 64;  // keys per wave: a multiple of 64
+    const int first = min(wave * keys, D + 1), last = min(first + keys, D + 1);
+    int base = 0;
+    if (D + 1 > 64) {
+        int sum = 0;
+        for (int i = first + lane; i < last; i += 64)
+            for (int w = 0; w < runs; ++w) sum += cursor[w * (D + 1) + i];
 #pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                int up = __shfl_up(incl, d, 64);
-                if (tid >= d) incl += up;
-            }
-            int excl = base + incl - c;
-            if (i <= D) {
-                if (counts && i < D) counts[i] = c;
-                if (offsets) offsets[i] = excl;
-                for (int w = 0; w < runs; ++w) {
-                    const int n = cursor[w * (D + 1) + i];
-                    cursor[w * (D + 1) + i] = excl;
-                    excl += n;
-                }
-            }
-            base += __shfl(incl, 63, 64);
+        for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+        if (lane == 0) s_total[wave] = sum;
+        __syncthreads();
+        for (int w = 0; w < wave; ++w) base += s_total[w];
+    }
+    for (int i0 = first; i0 < last; i0 += 64) {
+        const int i = i0 + lane;
+        int c = 0;
+        if (i < last)
+            for (int w = 0; w < runs; ++w) c += cursor[w * (D + 1) + i];
+        int incl = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int up = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += up;
         }
+        int excl = base + incl - c;
+        if (i < last) {
+            if (counts && i < D) counts[i] = c;
+            if (offsets) offsets[i] = excl;
+            for (int w = 0; w < runs; ++w) {
+                const int n = cursor[w * (D + 1) + i];
+                cursor[w * (D + 1) + i] = excl;
+                excl += n;
+            }
+        }
+        base += __shfl(incl, 63, 64);
     }
     __syncthreads();
     for (int t0 = begin; t0 < end; t0 += 64) {

@@ -2,6 +2,7 @@
 keys than fit more than one histogram, every request the same key, all idle, indices out of range in a late run."""
 import numpy as np
 import pytest
+import torch
 
 import dz_synth as S
 from test_gpu_segment import _run
@@ -23,3 +24,24 @@ def test_runs(dz, T, D):
         ids[T - 1] = D
         _run(dz, c, ids, D)
         assert dz.dz_check(c.h) == dz.DZ_ERR_INDEX
+
+
+def test_a_prefix_sum_over_many_keys_is_shared_by_the_waves(dz):
+    """One request over 8192 keys takes less than four calls over one key (a prefix sum walked by one wave alone: seven);
+    the best of several runs of back-to-back calls."""
+    with dz.Context(0) as c:
+        ids = torch.zeros(1, dtype=torch.int32, device="cuda")
+        perm = torch.empty(1, dtype=torch.int32, device="cuda")
+        best = {}
+        for rep in range(6):
+            for D in (1, 8192):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                for i in range(51):
+                    if i == 1:
+                        a.record()
+                    dz.dz_segment(c.h, ids, 1, D, None, None, perm)
+                b.record()
+                torch.cuda.synchronize()
+                best[D] = min(best.get(D, 1e9), a.elapsed_time(b) * 20)
+        print(f"us a call: {best}", flush=True)
+        assert best[8192] < 4 * best[1], best

@@ -274,8 +274,18 @@ struct TileShape {
     int twr, trt, tj;
     int rows() const { return twr * trt * 16; }
     int cols() const { return TW / twr * tj * 16; }
+    size_t partial_bytes() const { return (size_t)trt * tj * TTHREADS * 16; }   // of one slice of one tile
 };
 const TileShape shapes[] = {{4, 4, 8}, {4, 4, 7}, {4, 4, 6}, {4, 4, 5}, {4, 4, 4}, {2, 7, 4}, {2, 6, 4}, {2, 5, 4}};
+
+struct TilePlan {
+    const TileShape *shape = nullptr;
+    int NRB = 0, nchunks = 0;           // row blocks (of all projections), blocks of request rows
+    int S = 1;                          // slices of k of the tiles of the last round
+    int whole_per_xcd = 0;              // tiles that run whole, per XCD
+    int sliced() const { return 8 * ((int)((long long)NRB * nchunks - 8 * whole_per_xcd + 7) / 8); }
+    size_t partial_bytes() const { return (size_t)sliced() * S * shape->partial_bytes(); }
+};
 
 template <bool GROUP>
 hipError_t launch_shape(const TileShape &t, const DzStreamArgs &a, const DzGroup &gp, int NRB, int nchunks, hipStream_t st)
@@ -308,6 +318,57 @@ bool dz_tile_fits(const DzStreamArgs &a, const DzGroup &gp)
     return (unsigned long long)a.T * a.K * 2ull < (1ull << 31);
 }
 
+// Tiles of a call: one workgroup per CU, the tiles of the full rounds whole, those of the last, partly filled round cut
+// into up to eight slices of k, of two k tiles at least, as many as still fit the CUs at once and `room` bytes of partial
+// tiles.  Of the shapes the call takes the one with the least estimated time.  The estimate is in us, from measurements on
+// a full chip: a step takes 0.75 + 0.87 times the tile's area in units of 256 x 256 (1.61 for 256 x 256, 1.51 for 224 x 256,
+// 1.30 for 160 x 256), a round some 6 more for its start and end, and a meeting moves the partial tiles of all slices twice.
+// With slices of the smaller shapes even one tile fills the chip: 128 x 1024 x 8192 39.9 us in slices of the narrower
+// kernel, 29.8 here.  T = 2048: 5120 x 5120 139 us with 256 x 256 tiles (160 for 256 CUs), 107 with 160 x 256 (256);
+// 13824 x 5120 272 us with 256 x 256 (432: the second round is 69 % full), 257 with 224 x 256 (496).
+static TilePlan plan_tiles(int P, const int *N, int T, int K, int cus, int force_splits, size_t room)
+{
+    TilePlan best;
+    double best_cost = 0;
+    const int n = cus > 0 ? cus : 256;
+    for (const TileShape &t : shapes) {
+        int rb = 0;                     // row blocks of all projections; a row block never spans two
+        for (int p = 0; p < P; ++p) rb += (N[p] + t.rows() - 1) / t.rows();
+        const int ch = (T + t.cols() - 1) / t.cols();
+        const long long tiles = (long long)rb * ch;
+        if (tiles > 0x3fffffff) continue;
+        int S = 1;
+        long long whole = tiles;
+        if (force_splits > 0) {
+            S = force_splits; whole = 0;
+        } else if (cus >= 8 && tiles % cus != 0) {
+            const int tail = (int)(tiles % cus), sliced = (tail + 7) / 8 * 8;       // (dealt out to the XCDs in eights)
+            const int fit = std::min({cus / sliced, 8, K / 512, (int)(room / ((size_t)sliced * t.partial_bytes()))});
+            if (fit > 1) { S = fit; whole = tiles - tail; }
+        }
+        const double area = t.rows() * t.cols() / 65536.0, step = 0.75 + 0.87 * area;
+        double cost = (double)((whole + n - 1) / n) * (step * (K / 64) + 6.0);
+        if (whole < tiles) cost += step * ((K / 64 + S - 1) / S) + 6.0 + 5.0 * S * area * ((double)(tiles - whole) * S / n);
+        if (!best.shape || cost < best_cost) {
+            best_cost = cost;
+            best.shape = &t; best.NRB = rb; best.nchunks = ch; best.S = S;
+            best.whole_per_xcd = S > 1 ? (int)(whole / 8) : (int)((tiles + 7) / 8);
+        }
+    }
+    return best;
+}
+
+// The plan of a call with 64 MB of room, for tests without a GPU: {waves along the rows, row tiles and column blocks of a
+// wave, k slices, tiles that run whole, tiles}.
+extern "C" void dz_tile_plan(int P, const int *N, int T, int K, int cus, int *plan)
+{
+    const TilePlan t = plan_tiles(P, N, T, K, cus, 0, (size_t)64 << 20);
+    if (!t.shape) return;
+    const int tiles = t.NRB * t.nchunks;
+    const int v[6] = {t.shape->twr, t.shape->trt, t.shape->tj, t.S, std::min(8 * t.whole_per_xcd, tiles), tiles};
+    for (int i = 0; i < 6; ++i) plan[i] = v[i];
+}
+
 int dz_launch_tile(dz_ctx *ctx, const DzStreamArgs &args, const DzGroup &group, hipStream_t st)
 {
     DzStreamArgs a = args;
@@ -315,71 +376,35 @@ int dz_launch_tile(dz_ctx *ctx, const DzStreamArgs &args, const DzGroup &group, 
     if (!dz_tile_fits(a, gp)) return DZ_ERR_SHAPE;
     int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
     cus -= cus % 8;
-    // One workgroup per CU: the tiles of the full rounds run whole, those of the last, partly filled round are cut
-    // into up to eight slices of k, of two k tiles at least, as many as still fit the CUs at once.  Of the shapes the call takes the one with
-    // the least estimated time.  The estimate is in us, from measurements on a full chip: a step takes 0.75 + 0.87
-    // times the tile's area in units of 256 x 256 (1.61 for 256 x 256, 1.51 for 224 x 256, 1.30 for 160 x 256), a
-    // round some 6 more for its start and end, and a meeting moves the partial tiles of all slices twice.
-    // With slices of the smaller shapes even one tile fills the chip: 128 x 1024 x 8192 39.9 us in slices of the
-    // narrower kernel, 29.8 here.  T = 2048: 5120 x 5120 139 us with 256 x 256 tiles (160 for 256 CUs), 107 with 160 x 256 (256); 13824 x 5120
-    // 272 us with 256 x 256 (432: the second round is 69 % full), 257 with 224 x 256 (496).
     // The partial tiles of a call take up to 64 MB, twice what dz_create makes room for.  A call that is being captured
     // into a graph without an eager call before it cannot grow the workspace: it takes the best split that fits.
-    size_t room = (size_t)64 << 20;
-    const TileShape *best = nullptr;
-    double best_cost = 0;
-    int NRB = 0, nchunks = 0;
-    auto choose = [&]() {
-        best = nullptr;
-        for (const TileShape &t : shapes) {
-            int rb = 0;                     // row blocks of all projections; a row block never spans two
-            for (int p = 0; p < gp.P; ++p) rb += (gp.N[p] + t.rows() - 1) / t.rows();
-            const int ch = (a.T + t.cols() - 1) / t.cols();
-            const long long tiles = (long long)rb * ch;
-            if (tiles > 0x3fffffff) continue;
-            int S = 1;
-            long long whole = tiles;
-            if (ctx->force_splits > 0) {
-                S = ctx->force_splits; whole = 0;
-            } else if (cus >= 8 && tiles % cus != 0) {
-                const int tail = (int)(tiles % cus), sliced = (tail + 7) / 8 * 8;       // (dealt out to the XCDs in eights)
-                const int fit = std::min({cus / sliced, 8, a.K / 512, (int)(room / ((size_t)sliced * t.trt * t.tj * TTHREADS * 16))});
-                if (fit > 1) { S = fit; whole = tiles - tail; }
-            }
-            const double area = t.rows() * t.cols() / 65536.0, step = 0.75 + 0.87 * area, n = cus > 0 ? cus : 256;
-            double cost = (double)((whole + (long long)n - 1) / (long long)n) * (step * (a.K / 64) + 6.0);
-            if (whole < tiles) cost += step * ((a.K / 64 + S - 1) / S) + 6.0 + 5.0 * S * area * ((double)(tiles - whole) * S / n);
-            if (!best || cost < best_cost) {
-                best = &t; best_cost = cost; NRB = rb; nchunks = ch;
-                a.S = S; a.max_slots = S > 1 ? (int)(whole / 8) : (int)((tiles + 7) / 8);
-            }
-        }
-    };
-    choose();
-    if (best && a.S > 1 && 8ull * ((NRB * (long long)nchunks - 8 * a.max_slots + 7) / 8) * a.S * best->trt * best->tj * TTHREADS * 16 > ctx->partial_bytes) {
+    TilePlan plan = plan_tiles(gp.P, gp.N, a.T, a.K, cus, ctx->force_splits, (size_t)64 << 20);
+    if (plan.shape && plan.S > 1 && plan.partial_bytes() > ctx->partial_bytes) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         const hipError_t e = hipStreamIsCapturing(st, &cs);
         if (e != hipSuccess) return dz_set_hip_error(ctx, e);
-        if (cs != hipStreamCaptureStatusNone && ctx->force_splits == 0) { room = ctx->partial_bytes; choose(); }
+        if (cs != hipStreamCaptureStatusNone && ctx->force_splits == 0)
+            plan = plan_tiles(gp.P, gp.N, a.T, a.K, cus, 0, ctx->partial_bytes);
     }
-    if (!best) return DZ_ERR_SHAPE;
+    if (!plan.shape) return DZ_ERR_SHAPE;
+    const TileShape &shape = *plan.shape;
     gp.rb_start[0] = 0;
     for (int p = 0; p < DZ_MAX_GROUP; ++p)
-        gp.rb_start[p + 1] = gp.rb_start[p] + (p < gp.P ? (gp.N[p] + best->rows() - 1) / best->rows() : 0);
-    const int tiles = NRB * nchunks;
-    if (a.S > a.K / 256) a.S = a.K / 256;
-    const size_t tile_bytes = (size_t)best->trt * best->tj * TTHREADS * 16;
-    const int sliced = 8 * ((tiles - 8 * a.max_slots + 7) / 8);
-    if (a.S > 1 && (size_t)sliced * a.S * tile_bytes >= ((size_t)1 << 32)) a.S = 1;     // 32-bit byte offsets
-    if (a.S <= 1) { a.S = 1; a.max_slots = (tiles + 7) / 8; }
-    if (a.S > 1) {
-        int rc = dz_ensure_partial(ctx, (size_t)sliced * a.S * tile_bytes, st);
-        if (rc == DZ_OK) rc = dz_ensure_counters(ctx, sliced, st);
+        gp.rb_start[p + 1] = gp.rb_start[p] + (p < gp.P ? (gp.N[p] + shape.rows() - 1) / shape.rows() : 0);
+    const int tiles = plan.NRB * plan.nchunks;
+    if (plan.S > a.K / 256) plan.S = a.K / 256;
+    if (plan.S > 1 && plan.partial_bytes() >= ((size_t)1 << 32)) plan.S = 1;     // 32-bit byte offsets
+    if (plan.S <= 1) { plan.S = 1; plan.whole_per_xcd = (tiles + 7) / 8; }
+    if (plan.S > 1) {
+        int rc = dz_ensure_partial(ctx, plan.partial_bytes(), st);
+        if (rc == DZ_OK) rc = dz_ensure_counters(ctx, plan.sliced(), st);
         if (rc != DZ_OK) return rc;
     }
+    a.S = plan.S;
+    a.max_slots = plan.whole_per_xcd;
     a.partial = ctx->partial;
     a.counters = ctx->counters;
-    if (gp.P > 1) return dz_set_hip_error(ctx, launch_shape<true>(*best, a, gp, NRB, nchunks, st));
+    if (gp.P > 1) return dz_set_hip_error(ctx, launch_shape<true>(shape, a, gp, plan.NRB, plan.nchunks, st));
     a.N = gp.N[0]; a.W = gp.W[0]; a.out = gp.out[0];
-    return dz_set_hip_error(ctx, launch_shape<false>(*best, a, gp, NRB, nchunks, st));
+    return dz_set_hip_error(ctx, launch_shape<false>(shape, a, gp, plan.NRB, plan.nchunks, st));
 }

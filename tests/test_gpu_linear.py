@@ -160,13 +160,13 @@ def test_tiles_of_one_delta(dz):
 
 
 @pytest.mark.parametrize("opts", [{"DZ_OPT_WIDE_TILE": 2}, {"DZ_OPT_WIDE_TILE": 2, "DZ_OPT_SPLIT_K": 3},
-                                  {"DZ_OPT_WIDE_TILE": 2, "DZ_OPT_SPLIT_K": 1}, {}],
-                         ids=["wide", "wide_splits3", "wide_whole", "default"])
+                                  {"DZ_OPT_WIDE_TILE": 2, "DZ_OPT_SPLIT_K": 1}, {}, {"DZ_OPT_WIDE_TILE": 0},
+                                  {"DZ_OPT_WIDE_TILE": 0, "DZ_OPT_SPLIT_K": 1}, {"DZ_OPT_WIDE_TILE": 0, "DZ_OPT_SPLIT_K": 3}],
+                         ids=["wide", "wide_splits3", "wide_whole", "default", "narrow", "narrow_whole", "narrow_splits3"])
 def test_base_gemm_of_a_large_batch_over_several_tiles(dz, opts):
-    """The base product of a large batch (Eq. (2), first term): several 256 x 256 tiles with ragged
-    last tiles in both directions, whole and cut into k slices (DZ_OPT_WIDE_TILE = 2 sends every such
-    call to the 256 x 256 kernel, which by default only takes calls with many tiles), and the default
-    route."""
+    """The base product of a large batch (Eq. (2), first term): several tiles with ragged last tiles in
+    both directions, whole and cut into k slices, in the wide tile kernel (the default route, and
+    DZ_OPT_WIDE_TILE = 2) and in the narrower one (DZ_OPT_WIDE_TILE = 0)."""
     import oracle
     T, N, K = 600, 784, 1024
     print(f"wide base gemm {opts}", flush=True)

@@ -42,8 +42,11 @@ def test_group_of_projections_in_one_tiled_launch(dz, group, idle):
 
 
 # sizes that take each tile shape of the base product in turn, whole and in slices of k, with ragged last tiles
+# (tests/test_tile_plan.py checks that they do)
 BASE = [(65, 16, 256), (65, 16, 1024), (128, 272, 4096), (130, 3088, 2048), (500, 11024, 1024), (1000, 6160, 1024),
-        (1000, 8208, 256), (1000, 11024, 256), (1500, 8208, 256), (1500, 11024, 2048), (2049, 272, 2048), (2049, 8208, 1024)]
+        (1000, 8208, 256), (1000, 11024, 256), (1500, 8208, 256), (1500, 11024, 2048), (2049, 272, 2048), (2049, 8208, 1024),
+        (161, 1296, 4096), (385, 10960, 1024), (641, 336, 4096), (641, 13072, 256), (641, 13616, 256), (1000, 13104, 256),
+        (2049, 2832, 1536), (2049, 6416, 256)]
 
 
 @pytest.mark.parametrize("T,N,K", BASE)

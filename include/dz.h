@@ -38,7 +38,9 @@
  * and a HIP graph recorded before the growth can still be replayed).
  * A stream that is being captured into a HIP graph can be passed once an eager call with the same
  * shapes has sized the workspace: the calls then record only kernels.  A call that would have to
- * grow the workspace during a capture returns DZ_ERR_HIP and records nothing.
+ * grow the workspace during a capture returns DZ_ERR_HIP and records nothing -- except base products
+ * without deltas on more than 64 rows, which then cut k into the slices that fit the workspace as it is
+ * (unless DZ_OPT_SPLIT_K gives their number): their fp32 sums may be added in another order than eagerly.
  * Otherwise all compute entry points only enqueue work on `stream` (a hipStream_t passed as
  * void*, NULL = the default stream) and return; nothing is synchronised except in dz_check and
  * dz_destroy.  One dz_ctx serves one stream at a time.  x and out must not overlap.
@@ -89,8 +91,8 @@ int dz_destroy(dz_ctx *ctx);
 #define DZ_OPT_WORKGROUPS            2  /* workgroups per launch of the streaming kernel; 0 = eight waves per compute unit            */
 #define DZ_OPT_ROUND_TILES           3  /* k tiles of x a workgroup of the streaming kernel stages at once; 0 = as many as fit        */
 #define DZ_OPT_LARGE_BATCH_STREAMING 4  /* 1 = batches of more than 64 rows also go through the streaming kernel, 64 rows at a time  */
-#define DZ_OPT_WIDE_TILE             5  /* dz_base_gemm on more than 64 rows: 0 = never the wide tile kernel, 1 = where it is the faster
-                                           (default: everywhere it can run), 2 = everywhere it can run                                */
+#define DZ_OPT_WIDE_TILE             5  /* base products without deltas on more than 64 rows: 0 = never the wide tile kernel, 1 (default)
+                                           and 2 = wherever it can run (every weight of the call below 2 GiB)                         */
 #define DZ_OPT_REUSE_SEGMENTS        6  /* 1 = the caller promises that a token_to_delta vector passed again at the same address
                                            with the same T and D is unchanged: consecutive large-batch calls of one layer then share
                                            one sort.  Setting the option (to either value) forgets the remembered order.             */
@@ -125,6 +127,7 @@ int dz_pack_delta(dz_ctx *ctx, const uint8_t *codes, const uint8_t *idx, const v
  * that contains zero, rounded to nearest (half to even) in fp32:
  *   s = f16((hi - lo) / (2^bits - 1)) with lo = min(0, min v), hi = max(0, max v) over the group's kept
  *   values (s = 1, z = 0 if that is zero), z = clamp(rint((0 - lo) / s)) (never a negative zero), code = clamp(rint(v / s) + z).
+ * A NaN counts as the largest magnitude, has no part in lo and hi and gets code 0.
  */
 int dz_compress_delta(dz_ctx *ctx, const void *delta_f16, int N, int K, int bits, int group,
                       uint8_t *codes, uint8_t *idx, void *scale_f16, void *zero_f16, void *stream);
@@ -228,11 +231,11 @@ int dz_merge_delta(dz_ctx *ctx, const void *W_f16, const void *packed, int N, in
  * Several linear layers that read the same x for the same requests -- the q, k, v projections of a
  * transformer layer, or gate and up -- in one call:
  *   out[p][t] = f16( x[t] . W[p]^T + x[t] . Delta[p][token_to_delta[t]]^T ),   p = 0 .. P-1,
- * each exactly what dz_linear computes for projection p alone.  The base and delta products of a
- * layer are independent per output feature (Section 5.1, Eq. (2)), so stacking projections along
- * the output dimension changes no result; all P projections go
- * through one kernel launch, which saves the fixed cost of P - 1 launches (Section 5.2 argues the
- * same way for batching all deltas of a layer into one launch).
+ * each what dz_linear computes for projection p alone, to the order of the fp32 sums: the number of
+ * slices k is cut into is chosen for the whole call, so the last bits may differ.  The base and delta products of a
+ * layer are independent per output feature (Section 5.1, Eq. (2)), so projections can be stacked along the output
+ * dimension; all P go through one kernel launch, which saves the fixed cost of P - 1 launches (Section 5.2 argues
+ * the same way for batching all deltas of a layer into one launch).
  *   W, out          HOST arrays of P DEVICE pointers; N a HOST array of P output sizes
  *   packed_deltas   HOST array of P * D DEVICE pointers, projection-major: [p * D + m] is delta m
  *                   packed for projection p (shape N[p] x K)

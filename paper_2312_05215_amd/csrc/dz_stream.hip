@@ -634,9 +634,10 @@ void stream_kernel(DzStreamArgs a, DzGroup gp, DzGroupPtrs dp, int NRB, int roun
             constexpr int ITEMS = 16 * J * nq / THREADS; // four outputs of one request each, per thread
             static_assert(ITEMS * THREADS == 16 * J * nq, "every thread adds the same number of items");
             // All items of a thread and up to SL slots are requested at once: the loads come from beyond the L2s, and
-            // the last workgroup of a row block has nothing else to do while they travel.  At most 16 to 24 loads, what
-            // fits beside the weights already requested for the next piece.  T = 64, 1024 x 1024: 18.0 -> 16.2 us, a 70B
-            // layer 636 -> 631 us, a 7B layer with 32 deltas 337 -> 333 us against one item after the other.
+            // the last workgroup of a row block has nothing else to do while they travel.  SL * ITEMS is 16, 12 and 16
+            // loads for J = 2, 3 and 4, what fits beside the weights already requested for the next piece.  Against one
+            // item after the other, 3 deltas, T = 64: 1024 x 1024 15.6 -> 13.8 us, 1024 x 8192 27.2 -> 25.3, q,k,v of 4096 x
+            // 4096 43.2 -> 41.9, gate,up of 11008 x 4096 74.2 -> 71.0; T = 40: 13.4 -> 12.9 to no change; T = 17: no change.
             auto meet = [&](auto slots_at_once) {
                 constexpr int SL = decltype(slots_at_once)::value;
                 f4 sum[ITEMS];

@@ -118,3 +118,34 @@ def test_lora_reduction_over_lanes_and_waves(dz, T, N, K, r):
         dz.dz_lora_sbmm(c.h, x.cuda(), [a.cuda() for a in A], [b.cuda() for b in B], r, ids.cuda(), out, T, N, K, 0)
         torch.cuda.synchronize()
         assert_close(out, want, "lora")
+
+
+@pytest.mark.parametrize("bits,G", FORMATS)
+def test_compress_takes_a_nan_for_the_largest_magnitude(dz, bits, G):
+    """A NaN (quiet or signalling, either sign) is kept, stores code 0 and leaves the rest of its group as it is: the same
+    tables as with a value inside the group's range in its place that is the largest of its four."""
+    N, K = 16, 512
+    print(f"case bits={bits} G={G}", flush=True)
+    d = S._normal_f16((N, K), 0.002, S.stream(35, "nan", bits, G)).numpy().copy()
+    d[:, 0::G] = 0.02                                        # the range of every group, in its first and third four
+    d[:, 8::G] = -0.02
+    cols = np.arange(4, K, G) + np.arange(K // G) % 4        # one entry of the second four, each position in turn
+    stand = d.copy()
+    stand[:, cols] = 0.0175
+    d.view(np.uint16)[:, cols] = np.resize(np.array([0x7e00, 0x7d01, 0xfe00, 0xfdff], np.uint16), (N, len(cols)))
+    wc, wi, ws, wz = oracle.compress_.compress(stand, bits, G)
+    slot = (cols // 4) * 2                                   # the two kept entries of the four that holds the NaN
+    at = cols % 4
+    wc = wc.copy()
+    for s, p in zip(slot, at):
+        for j in range(2):
+            wc[:, s + j] = np.where(wi[:, s + j] == p, 0, wc[:, s + j])
+        assert ((wi[:, s] == p) | (wi[:, s + 1] == p)).all()
+    out = [torch.empty(N * n, dtype=t, device="cuda") for n, t in ((K // 2, torch.uint8), (K // 2, torch.uint8),
+                                                                   (K // G, torch.float16), (K // G, torch.float16))]
+    with dz.Context(0) as c:
+        dz.dz_compress_delta(c.h, torch.from_numpy(d).cuda(), N, K, bits, G, *out)
+        torch.cuda.synchronize()
+    for got, want in zip(out, (wc, wi, ws, wz)):
+        got = got.cpu().numpy().reshape(want.shape)
+        assert np.array_equal(got.view(np.uint8), np.ascontiguousarray(want).view(np.uint8).reshape(got.view(np.uint8).shape))

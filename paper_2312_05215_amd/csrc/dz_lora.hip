@@ -13,7 +13,9 @@
 //   expand: y[t] = B_m . u[t]  -- one thread per (request, 4 outputs), fp32, one rounding at the store.
 // The requests keep their own order.  Sorting them by adapter first cost a launch of its own and brought
 // nothing: neighbouring workgroups run on different XCDs, and what all requests read of the adapters for one
-// set of 8 ranks (D x 16 K bytes) stays in the L2s either way.
+// set of 8 ranks (D x 16 K bytes) stays in the L2s either way.  Larger calls do not miss it: on T = 1 .. 2048, K = 1024 ..
+// 8192, up to 128 adapters of rank 64, mixed and in runs, a call took 0.2 to 0.97 times as long as with the sort (T = 2048,
+// 32 adapters of rank 64, 8192 x 8192: 851 -> 655 us mixed, 596 -> 565 in runs).
 // T = 64, rank 16, 4096 x 4096: shrink 4.4 us and expand 4.1 us; with one wave per shrink workgroup behind
 // a sort of the requests it was 7.3 + 3.8 us and 3.9 us for the sort.
 #include "dz_internal.h"

@@ -157,12 +157,19 @@ def test_copies_of_the_next_batch_run_under_the_compute_of_this_one(dz):
         cache = dz.dz_cache_create(0, slots, nbytes)
         copy_stream = torch.cuda.Stream()
         batches = [[0, 1], [2, 3], [4, 5], [0, 1], [2, 3]]             # every batch after the second evicts
-        n_launch = 40                                                   # launches per batch: a few ms of compute
+        n_launch = 40                                                   # launches per batch: about a millisecond of compute
+        # inputs and outputs are on the device before the loop: an upload inside it would wait for the compute enqueued so
+        # far, and on a slow host the copies of the next batch are over before the next launches are even enqueued
+        local_ids, outs = [], []
+        for names in batches:
+            ids = torch.tensor([names[i % 2] for i in range(T)], dtype=torch.int32)
+            local = {m: i for i, m in enumerate(names)}
+            local_ids.append(torch.tensor([local[int(m)] for m in ids], dtype=torch.int32, device="cuda"))
+            outs.append((torch.full((T, N), 7.0, dtype=torch.float16, device="cuda"), ids))
         try:
             ev = lambda: torch.cuda.Event(enable_timing=True)
             origin = ev()
             spans = []      # per batch: (copy start, copy end, compute start, compute end) events
-            outs = []
             torch.cuda.synchronize()
             origin.record()
             acq = []
@@ -180,10 +187,7 @@ def test_copies_of_the_next_batch_run_under_the_compute_of_this_one(dz):
                     c1.record(copy_stream)
                     copy_ev.append((c0, c1))
                 rc, ptrs, s, h, ticket = acq[b]
-                local = {m: i for i, m in enumerate(names)}
-                ids = torch.tensor([names[i % 2] for i in range(T)], dtype=torch.int32)
-                lid = torch.tensor([local[int(m)] for m in ids], dtype=torch.int32, device="cuda")
-                o = torch.full((T, N), 7.0, dtype=torch.float16, device="cuda")
+                lid, o = local_ids[b], outs[b][0]
                 k0, k1 = ev(), ev()
                 dz.dz_cache_wait(cache, ticket)
                 k0.record()
@@ -192,7 +196,6 @@ def test_copies_of_the_next_batch_run_under_the_compute_of_this_one(dz):
                 k1.record()
                 dz.dz_cache_release(cache, ticket)
                 spans.append((k0, k1))
-                outs.append((o, ids))
             torch.cuda.synchronize()
             assert dz.dz_check(c.h) == dz.DZ_OK
             t = lambda e: origin.elapsed_time(e)

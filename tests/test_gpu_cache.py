@@ -157,7 +157,11 @@ def test_copies_of_the_next_batch_run_under_the_compute_of_this_one(dz):
         cache = dz.dz_cache_create(0, slots, nbytes)
         copy_stream = torch.cuda.Stream()
         batches = [[0, 1], [2, 3], [4, 5], [0, 1], [2, 3]]             # every batch after the second evicts
-        n_launch = 40                                                   # launches per batch: about a millisecond of compute
+        # Launches per batch.  A copy interval counts from its enqueuing, so it holds the wait for the compute of the batch
+        # before, and the copies themselves (13.6 MB, 0.27 ms) are the most that can lie under the next compute.  A quarter
+        # of the shorter interval is wanted: with 40 launches (0.76 ms) that is 0.19 of the 0.27 ms, and a host that enqueued
+        # a compute 0.1 ms late missed it; with 20 it is 0.1.
+        n_launch = 20
         # inputs and outputs are on the device before the loop: an upload inside it would wait for the compute enqueued so
         # far, and on a slow host the copies of the next batch are over before the next launches are even enqueued
         local_ids, outs = [], []

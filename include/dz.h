@@ -91,8 +91,11 @@ int dz_destroy(dz_ctx *ctx);
 #define DZ_OPT_WORKGROUPS            2  /* workgroups per launch of the streaming kernel; 0 = eight waves per compute unit            */
 #define DZ_OPT_ROUND_TILES           3  /* k tiles of x a workgroup of the streaming kernel stages at once; 0 = as many as fit        */
 #define DZ_OPT_LARGE_BATCH_STREAMING 4  /* 1 = batches of more than 64 rows also go through the streaming kernel, 64 rows at a time  */
-#define DZ_OPT_WIDE_TILE             5  /* base products without deltas on more than 64 rows: 0 = never the wide tile kernel, 1 (default)
-                                           and 2 = wherever it can run (every weight of the call below 2 GiB)                         */
+#define DZ_OPT_WIDE_TILE             5  /* more than 64 rows.  Base products without deltas: 0 = never the wide tile kernel, 1 (default) and
+                                           2 = wherever it can run (every weight of the call below 2 GiB).  Base and 2:4 deltas: 0 =
+                                           never the fused kernel, 1 = where it is estimated to be faster, 2 = wherever it can run
+                                           (W and x below 2 GiB, DZ_OPT_SPLIT_K 0); its fp32 sums are added in an order that depends
+                                           on the lengths of the segments                                                            */
 #define DZ_OPT_REUSE_SEGMENTS        6  /* 1 = the caller promises that a token_to_delta vector passed again at the same address
                                            with the same T and D is unchanged: consecutive large-batch calls of one layer then share
                                            one sort.  Setting the option (to either value) forgets the remembered order.             */

@@ -133,13 +133,17 @@ static int ensure_seg(dz_ctx *ctx, int T, hipStream_t st)
     if (int rc = quiesce_for_growth(ctx, st)) return rc;
     if (int rc = retire(ctx, ctx->seg_perm)) return rc;
     if (int rc = retire(ctx, ctx->seg_key)) return rc;
+    if (int rc = retire(ctx, ctx->seg_plan)) return rc;
     ctx->seg_perm = ctx->seg_key = nullptr;
+    ctx->seg_plan = nullptr;
     ctx->seg_cap = 0;
     ctx->seg_ids = nullptr;
     int want = T * 2;
     hipError_t e = hipMalloc((void **)&ctx->seg_perm, (size_t)want * 4);
     if (e != hipSuccess) return dz_set_hip_error(ctx, e);
     e = hipMalloc((void **)&ctx->seg_key, (size_t)want * 4);
+    if (e != hipSuccess) return dz_set_hip_error(ctx, e);
+    e = hipMalloc((void **)&ctx->seg_plan, (size_t)(1 + dz_fused_tiles_max(want, DZ_MAX_DELTAS)) * sizeof(DzFusedTile));
     if (e != hipSuccess) return dz_set_hip_error(ctx, e);
     ctx->seg_cap = want;
     return DZ_OK;
@@ -192,6 +196,8 @@ int dz_create(dz_ctx **out, int device)
         ctx->seg_cap = 4096;
         e = hipMalloc((void **)&ctx->seg_perm, (size_t)ctx->seg_cap * 4);
         if (e == hipSuccess) e = hipMalloc((void **)&ctx->seg_key, (size_t)ctx->seg_cap * 4);
+        if (e == hipSuccess)
+            e = hipMalloc((void **)&ctx->seg_plan, (size_t)(1 + dz_fused_tiles_max(ctx->seg_cap, DZ_MAX_DELTAS)) * sizeof(DzFusedTile));
     }
     if (e == hipSuccess) {
         ctx->counters_cap = 8192;
@@ -222,6 +228,7 @@ int dz_destroy(dz_ctx *ctx)
         if (ctx->seg_offsets) (void)hipFree(ctx->seg_offsets);
         if (ctx->seg_perm) (void)hipFree(ctx->seg_perm);
         if (ctx->seg_key) (void)hipFree(ctx->seg_key);
+        if (ctx->seg_plan) (void)hipFree(ctx->seg_plan);
         if (ctx->counters) (void)hipFree(ctx->counters);
         if (ctx->partial) (void)hipFree(ctx->partial);
         if (ctx->lora_u) (void)hipFree(ctx->lora_u);
@@ -271,7 +278,7 @@ int dz_segment(dz_ctx *ctx, const int32_t *ids, int T, int D, int32_t *counts, i
         return DZ_ERR_ALIGN;
     DeviceGuard guard(ctx->device);
     // T == 0 still has to produce counts = 0 and offsets = 0: the kernel handles an empty loop
-    return dz_launch_segment(ctx, ids, T, D, counts, offsets, perm, nullptr, (hipStream_t)stream);
+    return dz_launch_segment(ctx, ids, T, D, counts, offsets, perm, nullptr, nullptr, (hipStream_t)stream);
 }
 
 // P projections that share x and the request indices, in one launch.
@@ -309,23 +316,6 @@ static int run_group(dz_ctx *ctx, const void *x, int P, const void *const *W, co
     a.has_delta = has_delta && (D > 0 || !has_base);
     a.quant_only = quant_only ? 1 : 0;
     a.err_flag = ctx->err_flag;
-    const bool tiled = T > 64 && !ctx->no_prefill;      // large batches: MFMA-bound tiled kernel
-    if (has_delta && D > 0 && T <= 64) {
-        a.ids = ids;                    // small batches are sorted inside the streaming kernel
-    } else if (has_delta && D > 0) {
-        int rc = ensure_seg(ctx, T, st);
-        if (rc) return rc;
-        // With DZ_OPT_REUSE_SEGMENTS the caller promises that an index vector at the same address with
-        // the same T and D still holds the same values: the projections of one layer then share one sort.
-        const bool same = ctx->reuse_segments && ctx->seg_ids == ids && ctx->seg_T == T && ctx->seg_D == D;
-        if (!same) {
-            rc = dz_launch_segment(ctx, ids, T, D, nullptr, nullptr, ctx->seg_perm, ctx->seg_key, st);
-            if (rc) return rc;
-            ctx->seg_ids = ids; ctx->seg_T = T; ctx->seg_D = D;
-        }
-        a.perm = ctx->seg_perm;
-        a.key = ctx->seg_key;
-    }
     // all projections in one launch: small batches in the HBM-bound streaming kernel, large ones in the tiled kernel
     DzGroup gp;
     DzGroupPtrs dp;
@@ -339,6 +329,24 @@ static int run_group(dz_ctx *ctx, const void *x, int P, const void *const *W, co
     }
     if (has_delta)
         for (int m = 0; m < P * D; ++m) dp.p[m] = deltas[m];
+    const bool tiled = T > 64 && !ctx->no_prefill;      // large batches: MFMA-bound tiled kernel
+    if (has_delta && D > 0 && T <= 64) {
+        a.ids = ids;                    // small batches are sorted inside the streaming kernel
+    } else if (has_delta && D > 0) {
+        int rc = ensure_seg(ctx, T, st);
+        if (rc) return rc;
+        // With DZ_OPT_REUSE_SEGMENTS the caller promises that an index vector at the same address with
+        // the same T and D still holds the same values: the projections of one layer then share one sort.
+        const bool plan = tiled && dz_fused_takes(ctx, a, gp);
+        const bool same = ctx->reuse_segments && ctx->seg_ids == ids && ctx->seg_T == T && ctx->seg_D == D && (ctx->seg_planned || !plan);
+        if (!same) {
+            rc = dz_launch_segment(ctx, ids, T, D, nullptr, nullptr, ctx->seg_perm, ctx->seg_key, plan ? ctx->seg_plan : nullptr, st);
+            if (rc) return rc;
+            ctx->seg_ids = ids; ctx->seg_T = T; ctx->seg_D = D; ctx->seg_planned = plan;
+        }
+        a.perm = ctx->seg_perm;
+        a.key = ctx->seg_key;
+    }
     return tiled ? dz_launch_prefill(ctx, a, gp, dp, st) : dz_launch_stream(ctx, a, gp, dp, st);
 }
 

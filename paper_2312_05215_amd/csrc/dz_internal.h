@@ -14,6 +14,7 @@ struct dz_ctx {
     int32_t *seg_counts = nullptr;  // [DZ_SEG_MAX_D + 1]
     int32_t *seg_offsets = nullptr; // [DZ_SEG_MAX_D + 2]
     int seg_cap = 0;
+    struct DzFusedTile *seg_plan = nullptr;     // column tiles of the fused kernel for the present order (see DzFusedTile)
     float *partial = nullptr;       // split-K partial sums
     size_t partial_bytes = 0;
     int32_t *counters = nullptr;    // arrival counters, one per (chunk, row block); all zero between calls
@@ -38,7 +39,23 @@ struct dz_ctx {
     // the request order the last segment pass left in seg_perm / seg_key
     const int32_t *seg_ids = nullptr;
     int seg_T = -1, seg_D = -1;
+    bool seg_planned = false;       // ... and in seg_plan
 };
+
+// The fused kernel's column tiles: at most DZ_FUSED_BLOCKS blocks of 16 request rows, of at most two segments of the
+// sorted order; each segment begins at an even block.  Record 0 of a plan is its head; the tiles follow.
+#define DZ_FUSED_BLOCKS 16
+struct DzFusedTile {
+    int start0, rows0, key0;        // first segment: sorted position, rows, delta (D = none).  Head: number of tiles, the
+    int start1, rows1, key1;        //   dearest one's cost (dz_fused_cost).  Second segment, rows1 = 0 without
+    int pad[2];
+};
+// Cost of a step of a tile in units of the time of one column block (0.13 us on a full chip).  us a step, one tile on each CU,
+// 4-bit deltas: 1.46 with four blocks, 1.80 with 8, 2.06 with 10, 2.33 with 12, 2.61 with 14, 2.87 with 16.
+inline __host__ __device__ int dz_fused_cost(int blocks) { return blocks < 5 ? 11 : (blocks + 1) / 2 * 2 + 6; }
+// Most tiles of T rows over D deltas: a tile has eight blocks at least, or the ends of two segments, or is the last one before the
+// rows of the base model, or the last one.
+inline int dz_fused_tiles_max(int T, int D) { return (T / 16 + D + 1) / 8 + (D + 1) / 2 + 2; }
 
 #define DZ_SEG_MAX_D 8192
 
@@ -104,10 +121,12 @@ int dz_launch_pack(dz_ctx *, const uint8_t *, const uint8_t *, const void *, con
 int dz_launch_unpack(dz_ctx *, const void *, int, int, int, int, uint8_t *, uint8_t *, void *, void *,
                      float *, hipStream_t);
 int dz_launch_segment(dz_ctx *, const int32_t *ids, int T, int D, int32_t *counts, int32_t *offsets,
-                      int32_t *perm, int32_t *key, hipStream_t);
+                      int32_t *perm, int32_t *key, DzFusedTile *plan, hipStream_t);
 int dz_launch_stream(dz_ctx *, const DzStreamArgs &, const DzGroup &, const DzGroupPtrs &, hipStream_t);
 int dz_launch_prefill(dz_ctx *, const DzStreamArgs &, const DzGroup &, const DzGroupPtrs &, hipStream_t);
 int dz_launch_tile(dz_ctx *, const DzStreamArgs &, const DzGroup &, hipStream_t);
+bool dz_fused_takes(const dz_ctx *, const DzStreamArgs &, const DzGroup &);
+int dz_launch_fused(dz_ctx *, const DzStreamArgs &, const DzGroup &, const DzGroupPtrs &, hipStream_t);
 bool dz_tile_fits(const DzStreamArgs &, const DzGroup &);
 int dz_launch_qpack(dz_ctx *, const uint8_t *codes, const void *scale, const void *zero, int N, int K, int bits, int group,
                     void *packed, hipStream_t);

@@ -634,6 +634,7 @@ int dz_launch_prefill(dz_ctx *ctx, const DzStreamArgs &args, const DzGroup &gp, 
     // -> 400 at the largest), on groups of projections 0.5 to 1.1 times.  What is left to this one are calls in which
     // some weight has 2 GiB or more, and calls with DZ_OPT_WIDE_TILE = 0.
     if (ctx->tile_kernel && dz_tile_fits(args, gp)) return dz_launch_tile(ctx, args, gp, st);
+    if (dz_fused_takes(ctx, args, gp)) return dz_launch_fused(ctx, args, gp, dp, st);
     int rc = DZ_OK;
     // 8 waves x 2 row tiles measured faster than 4 x 4 (two waves per SIMD hide each other's waits)
     const hipError_t e = launch_pf_kind<8, 2, 8>(ctx, args, gp, dp, st, &rc);

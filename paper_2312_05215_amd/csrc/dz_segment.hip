@@ -40,16 +40,66 @@ __device__ inline int place(int32_t *cur, int key, bool active, int key_bits, in
     return __shfl(at, leader, 64) + (int)lanes_below(same);
 }
 
+// The column tiles of the fused kernel (DzFusedTile), by one thread: segments in their order, up to DZ_FUSED_BLOCKS blocks of
+// 16 rows and two segments a tile.  A segment that fills more than a tile is cut into equal ones, and the end of a segment
+// waits for the next segment unless it has ten blocks by itself and the next one does not fit whole: a step costs six
+// blocks' time beside the blocks', so few wide tiles are the cheapest.  (Lists for nine narrower limits as well, for each
+// launch to choose the one that fills its last round best, brought less than the pass grew by: 5 to 10 us.)
+__device__ void plan_tiles(const int32_t *start, int T, int D, DzFusedTile *plan)
+{
+    constexpr int CAP = DZ_FUSED_BLOCKS;
+    int n = 0, most = 0, o_start = 0, o_rows = 0, o_key = 0;        // the open tile's first segment, if it has rows
+    auto emit = [&](int s0, int r0, int k0, int s1, int r1, int k1) {
+        plan[++n] = DzFusedTile{s0, r0, k0, s1, r1, k1, {0, 0}};
+        most = max(most, dz_fused_cost((r1 ? (r0 + 31) >> 5 << 1 : (r0 + 15) >> 4) + ((r1 + 15) >> 4)));
+    };
+    for (int key = 0; key <= D; ++key) {
+        int at = start[key], rows = (key < D ? start[key + 1] : T) - at;
+        if (key == D && o_rows) {                       // rows of the base model have tiles of their own
+            emit(o_start, o_rows, o_key, 0, 0, 0);
+            o_rows = 0;
+        }
+        while (rows > 0) {
+            const int blocks = (rows + 15) >> 4, open = (o_rows + 31) >> 5 << 1;     // (a second segment begins at an even block)
+            int take = 0;                               // rows that leave with a tile
+            if (open == 0 && blocks <= CAP) {
+                o_start = at; o_rows = rows; o_key = key;
+                break;
+            }
+            if (open == 0) {
+                const int pieces = (blocks + CAP - 1) / CAP;
+                take = (blocks + pieces - 1) / pieces * 16;
+                emit(at, take, key, 0, 0, 0);
+            } else if (open + blocks <= CAP) {
+                take = rows;
+                emit(o_start, o_rows, o_key, at, take, key);
+            } else if (open >= 10) {
+                emit(o_start, o_rows, o_key, 0, 0, 0);
+            } else {
+                take = (CAP - open) * 16;
+                emit(o_start, o_rows, o_key, at, take, key);
+            }
+            o_rows = 0;
+            at += take;
+            rows -= take;
+        }
+    }
+    if (o_rows) emit(o_start, o_rows, o_key, 0, 0, 0);
+    plan[0] = DzFusedTile{n, most, 0, 0, 0, 0, {0, 0}};
+}
+
 // key = delta index, or D for "no delta" (index -1 or out of range).  `runs` waves share the requests.
 __global__ __launch_bounds__(SEG_THREADS) void segment_kernel(const int32_t *__restrict__ ids, int T, int D, int runs, int key_bits,
                                                               int32_t *__restrict__ counts,
                                                               int32_t *__restrict__ offsets,
                                                               int32_t *__restrict__ perm,
                                                               int32_t *__restrict__ key_out,
+                                                              DzFusedTile *__restrict__ plan,
                                                               int32_t *__restrict__ err_flag)
 {
     extern __shared__ int32_t cursor[];          // [runs][D + 1] histograms, then running write cursors
     __shared__ int32_t s_total[SEG_WAVES];       // requests of each wave's run of keys
+    __shared__ int32_t s_start[DZ_MAX_DELTAS + 2];       // first sorted position of each key, for the plan
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (int i = tid; i < runs * (D + 1); i += SEG_THREADS) cursor[i] = 0;
     __syncthreads();
@@ -95,6 +145,7 @@ __global__ __launch_bounds__(SEG_THREADS) void segment_kernel(const int32_t *__r
         if (i < last) {
             if (counts && i < D) counts[i] = c;
             if (offsets) offsets[i] = excl;
+            if (plan) s_start[i] = excl;
             for (int w = 0; w < runs; ++w) {
                 const int n = cursor[w * (D + 1) + i];
                 cursor[w * (D + 1) + i] = excl;
@@ -104,6 +155,7 @@ __global__ __launch_bounds__(SEG_THREADS) void segment_kernel(const int32_t *__r
         base += __shfl(incl, 63, 64);
     }
     __syncthreads();
+    if (plan && tid == SEG_THREADS - 1) plan_tiles(s_start, T, D, plan);
     for (int t0 = begin; t0 < end; t0 += 64) {
         const int t = t0 + lane, id = t < end ? ids[t] : -1;
         const int key = (id >= 0 && id < D) ? id : D;
@@ -118,7 +170,7 @@ __global__ __launch_bounds__(SEG_THREADS) void segment_kernel(const int32_t *__r
 }  // namespace
 
 int dz_launch_segment(dz_ctx *ctx, const int32_t *ids, int T, int D, int32_t *counts, int32_t *offsets,
-                      int32_t *perm, int32_t *key, hipStream_t st)
+                      int32_t *perm, int32_t *key, DzFusedTile *plan, hipStream_t st)
 {
     // as many runs as have 64 requests each and whose histograms fit (D <= DZ_SEG_MAX_D: one always does)
     const int fit = SEG_LDS / ((D + 1) * (int)sizeof(int32_t)), chunks = (T + 63) / 64;
@@ -128,6 +180,6 @@ int dz_launch_segment(dz_ctx *ctx, const int32_t *ids, int T, int D, int32_t *co
     while ((D >> key_bits) > 0) ++key_bits;
     const size_t lds = (size_t)runs * (D + 1) * sizeof(int32_t);
     hipLaunchKernelGGL(segment_kernel, dim3(1), dim3(SEG_THREADS), lds, st, ids, T, D, runs, key_bits, counts, offsets, perm, key,
-                       ctx->err_flag);
+                       plan, ctx->err_flag);
     return dz_set_hip_error(ctx, hipGetLastError());
 }

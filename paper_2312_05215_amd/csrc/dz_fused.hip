@@ -21,7 +21,7 @@
 //   * packed tiles wait in stage registers, loaded a step before they are needed.
 // us, 13824 x 5120, T = 2048, narrower kernel -> here (medians of seven turns): one delta 438 -> 384 (the rule below still leaves
 // that call to the narrower kernel), 8 segments of 256 rows 459 -> 402, 16 of 128 469 -> 434, 16 random ones 517 -> 483;
-// 777 x (2 x 11008) x 4096, 3 deltas 257 -> 242.  The chip runs at 1.5 to 1.8 GHz on random values, at 2.3 GHz on zeros.
+// 777 x (2 x 11008) x 4096, 3 deltas 257 -> 242 (left there too).  The chip runs at 1.5 to 1.8 GHz on random values, at 2.3 GHz on zeros.
 #include "dz_mma.h"
 #include <algorithm>
 #include <cmath>
@@ -436,10 +436,10 @@ hipError_t launch_fused(const DzStreamArgs &a, const DzGroup &gp, const DzGroupP
 // Estimated times of a call here and in the narrower kernel, in units of dz_fused_cost and steps.  The host knows T and D and
 // not the segments: it takes them to fill tiles of 16 blocks to nine tenths.  A step of the narrower kernel's tile of 128
 // columns takes 13 units where one segment has all of them, and up to 9 more the more of the tiles are mixed.
-static float fused_estimate(int NRB, int T, int D, int KT, int cus)
+static float fused_estimate(int NRB, int T, int D, int KT, int cus, int more)
 {
     const float blocks = (float)T / 16.f + 0.75f * (float)D;
-    const int n = std::max((int)std::ceil(blocks / (0.9f * DZ_FUSED_BLOCKS)), (D + 1) / 2);
+    const int n = std::max((int)std::ceil(blocks / (0.9f * DZ_FUSED_BLOCKS)), (D + 1) / 2) + more;
     const int wide = std::min(DZ_FUSED_BLOCKS, (int)std::ceil(blocks / (float)n));
     const long long M = (long long)NRB * n;
     float e;
@@ -461,12 +461,13 @@ static float narrow_estimate(int NRB, int T, int D, int KT, int cus)
 }
 
 // Does the fused kernel take this call?  Base and 2:4 deltas, every byte offset of W and x below 2^31 (a missing row is an
-// offset in the upper half), the number of k slices not given, 64 request rows a delta at least, and an estimate 10 % below the
-// narrower kernel's.  Of 115 random sizes with 64 rows a delta (T = 149 to 2009, 83 to 747 us) this sends 44 here: 0.67 to 1.04
-// times the narrower kernel's time, 0.89 in the geometric mean, six of them slower, one by more than 3 % (734 x (2 x 11008) x 8192,
-// four uneven deltas: 432 us there, 451 here).  A line at 0.95 takes 62 with the mean at 0.90 but up to 1.09:
-// 809 x 4096 x 11008, three segments of 17 blocks each, 147 us there and 160 here.  The host knows the mean segment only, so no
-// estimate tells that one from 777 rows, 162 us there and 135 here, which stays behind.  DZ_OPT_WIDE_TILE = 2 leaves the estimate out.
+// offset in the upper half), the number of k slices not given, 128 request rows a delta at least (half a tile: two segments of
+// that size fill one), and an estimate 5 % below the narrower kernel's, also with two column tiles more than even segments need:
+// the host does not know the segments' lengths, and uneven ones are what made looser rules wrong.  Chosen on 344 random sizes
+// (T = 65 to 2048, up to 32 deltas) and checked on 355 others: of those it sends 46 here, 0.86 times the narrower kernel's time in the
+// geometric mean, two of them slower (1127 x 5120 x 5120, eight uneven deltas, 151 us there and 157 here, is the worst).  64 rows
+// a delta and 10 %, without the two tiles, takes 155 of the 355, but 28 of them are slower, the worst 1.40 times.
+// DZ_OPT_WIDE_TILE = 2 leaves the estimate out.
 bool dz_fused_takes(const dz_ctx *ctx, const DzStreamArgs &a, const DzGroup &gp)
 {
     if (!ctx->tile_kernel || ctx->force_splits > 0 || !a.has_base || !a.has_delta || a.quant_only || a.T <= 64) return false;
@@ -480,8 +481,10 @@ bool dz_fused_takes(const dz_ctx *ctx, const DzStreamArgs &a, const DzGroup &gp)
     if (ctx->tile_kernel == 2) return true;
     int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
     cus = std::max(cus - cus % 8, 8);
-    return a.T >= 64 * a.D &&
-           fused_estimate((int)NRB, a.T, a.D, a.K / 256, cus) < 0.90f * narrow_estimate((int)NRB, a.T, a.D, a.K / 256, cus);
+    if (a.T < 128 * a.D) return false;
+    const int KT = a.K / 256;
+    const float e = std::max(fused_estimate((int)NRB, a.T, a.D, KT, cus, 0), fused_estimate((int)NRB, a.T, a.D, KT, cus, 2));
+    return e < 0.95f * narrow_estimate((int)NRB, a.T, a.D, KT, cus);
 }
 
 int dz_launch_fused(dz_ctx *ctx, const DzStreamArgs &args, const DzGroup &group, const DzGroupPtrs &dp, hipStream_t st)

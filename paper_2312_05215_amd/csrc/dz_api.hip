@@ -196,8 +196,6 @@ int dz_create(dz_ctx **out, int device)
         ctx->seg_cap = 4096;
         e = hipMalloc((void **)&ctx->seg_perm, (size_t)ctx->seg_cap * 4);
         if (e == hipSuccess) e = hipMalloc((void **)&ctx->seg_key, (size_t)ctx->seg_cap * 4);
-        if (e == hipSuccess)
-            e = hipMalloc((void **)&ctx->seg_plan, (size_t)(1 + dz_fused_tiles_max(ctx->seg_cap, DZ_MAX_DELTAS)) * sizeof(DzFusedTile));
     }
     if (e == hipSuccess) {
         ctx->counters_cap = 8192;
@@ -208,6 +206,8 @@ int dz_create(dz_ctx **out, int device)
         ctx->partial_bytes = (size_t)32 << 20;
         e = hipMalloc((void **)&ctx->partial, ctx->partial_bytes);
     }
+    if (e == hipSuccess)
+        e = hipMalloc((void **)&ctx->seg_plan, (size_t)(1 + dz_fused_tiles_max(ctx->seg_cap, DZ_MAX_DELTAS)) * sizeof(DzFusedTile));
     if (e != hipSuccess) {
         (void)dz_set_hip_error(nullptr, e);     // the context goes away: keep the text for dz_strerror
         dz_destroy(ctx);

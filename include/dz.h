@@ -41,6 +41,7 @@
  * grow the workspace during a capture returns DZ_ERR_HIP and records nothing -- except base products
  * without deltas on more than 64 rows, which then cut k into the slices that fit the workspace as it is
  * (unless DZ_OPT_SPLIT_K gives their number): their fp32 sums may be added in another order than eagerly.
+ * The fused kernel of base and deltas (DZ_OPT_WIDE_TILE) does the same; eagerly it may grow the workspace to 128 MB.
  * Otherwise all compute entry points only enqueue work on `stream` (a hipStream_t passed as
  * void*, NULL = the default stream) and return; nothing is synchronised except in dz_check and
  * dz_destroy.  One dz_ctx serves one stream at a time.  x and out must not overlap.

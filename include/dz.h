@@ -99,7 +99,9 @@ int dz_destroy(dz_ctx *ctx);
                                            on the lengths of the segments                                                            */
 #define DZ_OPT_REUSE_SEGMENTS        6  /* 1 = the caller promises that a token_to_delta vector passed again at the same address
                                            with the same T and D is unchanged: consecutive large-batch calls of one layer then share
-                                           one sort.  Setting the option (to either value) forgets the remembered order.             */
+                                           one sort.  Setting the option (to either value) forgets the remembered order.  Calls that
+                                           a stream capture records share a sort within that capture only.  A replayed graph sorts
+                                           into the same workspace: set the option again after a replay, before eager calls           */
 int dz_set_option(dz_ctx *ctx, int key, int value);
 
 /*

@@ -67,6 +67,18 @@ static int quiesce_for_growth(dz_ctx *ctx, hipStream_t st)
     return DZ_OK;
 }
 
+// The capture that `st` is part of, 0 if none (the default stream cannot be captured).
+static int capture_id(dz_ctx *ctx, hipStream_t st, unsigned long long &id)
+{
+    id = 0;
+    if (!st) return DZ_OK;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamGetCaptureInfo(st, &cs, &id);
+    if (e != hipSuccess) return dz_set_hip_error(ctx, e);
+    if (cs == hipStreamCaptureStatusNone) id = 0;
+    return DZ_OK;
+}
+
 // A buffer that a growth replaces is kept until dz_destroy: the kernel nodes of a HIP graph recorded
 // earlier still hold its address, and a replay must find it allocated.
 static int retire(dz_ctx *ctx, void *p)
@@ -337,12 +349,18 @@ static int run_group(dz_ctx *ctx, const void *x, int P, const void *const *W, co
         if (rc) return rc;
         // With DZ_OPT_REUSE_SEGMENTS the caller promises that an index vector at the same address with
         // the same T and D still holds the same values: the projections of one layer then share one sort.
+        // A sort that a capture records is made when the graph is replayed: the order serves that capture alone, and a graph
+        // does not rely on an eager sort, which the context's other calls overwrite before a replay.
+        unsigned long long capture = 0;
+        if (ctx->reuse_segments)
+            if (int crc = capture_id(ctx, st, capture)) return crc;
         const bool plan = tiled && dz_fused_takes(ctx, a, gp);
-        const bool same = ctx->reuse_segments && ctx->seg_ids == ids && ctx->seg_T == T && ctx->seg_D == D && (ctx->seg_planned || !plan);
+        const bool same = ctx->reuse_segments && ctx->seg_ids == ids && ctx->seg_T == T && ctx->seg_D == D &&
+                          ctx->seg_capture == capture && (ctx->seg_planned || !plan);
         if (!same) {
             rc = dz_launch_segment(ctx, ids, T, D, nullptr, nullptr, ctx->seg_perm, ctx->seg_key, plan ? ctx->seg_plan : nullptr, st);
             if (rc) return rc;
-            ctx->seg_ids = ids; ctx->seg_T = T; ctx->seg_D = D; ctx->seg_planned = plan;
+            ctx->seg_ids = ids; ctx->seg_T = T; ctx->seg_D = D; ctx->seg_capture = capture; ctx->seg_planned = plan;
         }
         a.perm = ctx->seg_perm;
         a.key = ctx->seg_key;

@@ -39,6 +39,7 @@ struct dz_ctx {
     // the request order the last segment pass left in seg_perm / seg_key
     const int32_t *seg_ids = nullptr;
     int seg_T = -1, seg_D = -1;
+    unsigned long long seg_capture = 0;     // the capture that recorded it, 0 = made eagerly
     bool seg_planned = false;       // ... and in seg_plan
 };
 

@@ -151,3 +151,32 @@ def test_small_base_products_are_captured_cold(dz, T, N, K):
             want = x.float() @ W.float().t()
             off = ((out.float() - want).abs() / torch.maximum(want.abs(), want.pow(2).mean().sqrt())).max().item()
             assert off < 1e-3, (rep, off)        # half a unit of fp16 in the last place and the order of fp32 sums
+
+
+def test_a_recorded_sort_is_not_taken_for_one_that_was_made(dz):
+    """DZ_OPT_REUSE_SEGMENTS and captures: the first call is a captured one, its graph has not run, and an eager call with the
+    same indices sorts for itself; the two projections of the graph share its own sort, whatever ran in between."""
+    import oracle
+    with dz.Context(0) as c:
+        c.set_option(dz.DZ_OPT_REUSE_SEGMENTS, 1)
+        a, b = (Case(dz, c.h, 70 + p, 150, N, 512, 6, 4, 128, "uniform") for p, N in enumerate((96, 64)))
+        oa, ob, oe = a.out(fill=7.0), b.out(fill=7.0), a.out(fill=7.0)
+        graph = torch.cuda.CUDAGraph()
+        print("recorded sort: capture", flush=True)
+        with torch.cuda.graph(graph):
+            dz.dz_linear(c.h, a.dx, a.dW, a.packed, a.dids, oa, a.T, a.N, a.K, a.bits, a.G)
+            dz.dz_linear(c.h, a.dx, b.dW, b.packed, a.dids, ob, b.T, b.N, b.K, b.bits, b.G)
+        want_b = oracle.c.linear(a.x.numpy(), b.W.numpy(), b.dense, a.ids.numpy())
+        for rep in range(3):
+            dz.dz_linear(c.h, a.dx, a.dW, a.packed, a.dids, oe, a.T, a.N, a.K, a.bits, a.G)
+            dz.dz_linear(c.h, b.dx, b.dW, b.packed, b.dids, ob, b.T, b.N, b.K, b.bits, b.G)      # another order
+            assert dz.dz_check(c.h) == dz.DZ_OK
+            assert_close(oe, a.y, f"eager {rep}")
+            assert_close(ob, b.y, f"eager other {rep}")
+            for o in (oa, ob, oe):
+                o.fill_(7.0)
+            graph.replay()
+            assert dz.dz_check(c.h) == dz.DZ_OK
+            assert_close(oa, a.y, f"replay {rep}")
+            assert_close(ob, want_b, f"replay {rep} second")
+            c.set_option(dz.DZ_OPT_REUSE_SEGMENTS, 1)        # the replay sorted into the same workspace

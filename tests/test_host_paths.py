@@ -1,0 +1,47 @@
+"""What the host side decides for a call, seen on a HIP runtime without a GPU (fake_hip.cpp): sorts, kernels, workspace."""
+import sys
+
+import pytest
+
+import fake_hip as F
+
+
+def captured_orders():
+    """DZ_OPT_REUSE_SEGMENTS: an order that a capture recorded has not been made, so neither an eager call nor another
+    capture may use it; nor may a graph rely on an order that eager calls make and overwrite."""
+    s = F.Sim()
+    s.option(F.REUSE_SEGMENTS, 1)
+    layer = lambda: (s.linear([4096], 4096, 8, 300), s.linear([64] * 3, 4096, 8, 300))
+    s.capture(7)
+    assert layer() == (0, 0)
+    assert s.kernels() == ["segment_kernel", "prefill_kernel", "prefill_kernel"], "one capture shares one sort"
+    s.capture(8)
+    assert layer() == (0, 0)
+    assert s.kernels() == ["segment_kernel", "prefill_kernel", "prefill_kernel"], "another capture sorts again"
+    s.capture(0)
+    assert layer() == (0, 0)
+    assert s.kernels() == ["segment_kernel", "prefill_kernel", "prefill_kernel"], "an eager call sorts again"
+    s.capture(9)
+    assert layer() == (0, 0)
+    assert s.kernels() == ["segment_kernel", "prefill_kernel", "prefill_kernel"], "a graph sorts for itself"
+    s.capture(0)
+    # the tile list of the fused kernel: recorded by a capture, asked for by an eager call after one that needed none
+    s.option(F.REUSE_SEGMENTS, 1)
+    s.option(F.WIDE_TILE, 0)
+    assert s.linear([4096], 4096, 8, 2048) == 0
+    s.option(F.WIDE_TILE, 2)
+    s.capture(10)
+    assert s.linear([4096], 4096, 8, 2048) == 0
+    s.capture(0)
+    s.launches()
+    assert s.linear([4096], 4096, 8, 2048) == 0
+    assert s.kernels() == ["segment_kernel", "fused_kernel"], "the list has not been made"
+
+
+@pytest.mark.parametrize("scenario", [captured_orders], ids=lambda f: f.__name__)
+def test_host(scenario, tmp_path):
+    F.run(__file__, scenario.__name__, tmp_path)
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[1]]()

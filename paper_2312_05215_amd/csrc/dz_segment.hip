@@ -17,7 +17,7 @@
 namespace {
 
 constexpr int SEG_WAVES = 16, SEG_THREADS = SEG_WAVES * 64;
-constexpr int SEG_LDS = 64 * 1024 - SEG_WAVES * 4;      // what a launch may use without an attribute, less s_total
+constexpr int SEG_LDS = 64 * 1024 - SEG_WAVES * 4;      // what a launch may use without an attribute, less s_total, the only static array
 
 __device__ inline unsigned lanes_below(unsigned long long m)
 {
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(SEG_THREADS) void segment_kernel(const int32_t *__r
 {
     extern __shared__ int32_t cursor[];          // [runs][D + 1] histograms, then running write cursors
     __shared__ int32_t s_total[SEG_WAVES];       // requests of each wave's run of keys
-    __shared__ int32_t s_start[DZ_MAX_DELTAS + 2];       // first sorted position of each key, for the plan
+    int32_t *const s_start = cursor + runs * (D + 1);    // first sorted position of each key: there only with a plan
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (int i = tid; i < runs * (D + 1); i += SEG_THREADS) cursor[i] = 0;
     __syncthreads();
@@ -172,13 +172,15 @@ __global__ __launch_bounds__(SEG_THREADS) void segment_kernel(const int32_t *__r
 int dz_launch_segment(dz_ctx *ctx, const int32_t *ids, int T, int D, int32_t *counts, int32_t *offsets,
                       int32_t *perm, int32_t *key, DzFusedTile *plan, hipStream_t st)
 {
-    // as many runs as have 64 requests each and whose histograms fit (D <= DZ_SEG_MAX_D: one always does)
-    const int fit = SEG_LDS / ((D + 1) * (int)sizeof(int32_t)), chunks = (T + 63) / 64;
+    // as many runs as have 64 requests each and whose histograms fit (D <= DZ_SEG_MAX_D: one always does), with one more of the
+    // same size where a plan is wanted (D <= DZ_MAX_DELTAS)
+    const int extra = plan ? 1 : 0;
+    const int fit = SEG_LDS / ((D + 1) * (int)sizeof(int32_t)) - extra, chunks = (T + 63) / 64;
     int runs = fit < SEG_WAVES ? fit : SEG_WAVES;
     if (runs > chunks) runs = chunks > 0 ? chunks : 1;
     int key_bits = 0;
     while ((D >> key_bits) > 0) ++key_bits;
-    const size_t lds = (size_t)runs * (D + 1) * sizeof(int32_t);
+    const size_t lds = (size_t)(runs + extra) * (D + 1) * sizeof(int32_t);
     hipLaunchKernelGGL(segment_kernel, dim3(1), dim3(SEG_THREADS), lds, st, ids, T, D, runs, key_bits, counts, offsets, perm, key,
                        plan, ctx->err_flag);
     return dz_set_hip_error(ctx, hipGetLastError());

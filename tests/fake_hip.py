@@ -20,6 +20,20 @@ def run(test_file, scenario, tmp_path):
     assert p.returncode == 0, p.stdout
 
 
+def static_lds(kernel):
+    """LDS bytes that the compiler gave kernels of this name in libdz.so, from the metadata of their code objects."""
+    import msgpack
+    data, at, found = open(LIBDZ, "rb").read(), 0, set()
+    while (at := data.find(b"AMDGPU\0\0", at + 1)) >= 0:      # ELF note: name size, size, type 32, name, contents
+        if data[at - 12:at - 8] == (7).to_bytes(4, "little") and data[at - 4:at] == (32).to_bytes(4, "little"):
+            size = int.from_bytes(data[at - 8:at - 4], "little")
+            for k in msgpack.unpackb(data[at + 8:at + 8 + size])["amdhsa.kernels"]:
+                if kernel in k[".name"]:
+                    found.add(k[".group_segment_fixed_size"])
+    assert found, kernel
+    return max(found)
+
+
 class Sim:
     """One context on the fake runtime.  Addresses are made up: nothing is ever read through them."""
 

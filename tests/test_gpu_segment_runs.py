@@ -45,3 +45,12 @@ def test_a_prefix_sum_over_many_keys_is_shared_by_the_waves(dz):
                 best[D] = min(best.get(D, 1e9), a.elapsed_time(b) * 20)
         print(f"us a call: {best}", flush=True)
         assert best[8192] < 4 * best[1], best
+
+
+@pytest.mark.parametrize("T,D", [(1025, 1014), (1025, 1022), (3000, 4091), (128, 8183)])
+def test_histograms_that_fill_lds(dz, T, D):
+    """Numbers of keys whose histograms leave next to nothing of the 64 KB that a launch may use."""
+    print(f"case T={T} D={D}", flush=True)
+    with dz.Context(0) as c:
+        _run(dz, c, S.ids_uniform(T, D, S.stream(62, "r", T, D)).numpy(), D)
+        assert dz.dz_check(c.h) == dz.DZ_OK

@@ -38,7 +38,22 @@ def captured_orders():
     assert s.kernels() == ["segment_kernel", "fused_kernel"], "the list has not been made"
 
 
-@pytest.mark.parametrize("scenario", [captured_orders], ids=lambda f: f.__name__)
+def sorts_fit_lds():
+    """Static and dynamic LDS of a sort together stay within what a launch may use without an attribute."""
+    s, static = F.Sim(), F.static_lds("segment_kernel")
+    for D in list(range(130)) + list(range(130, 8193, 11)) + [1014, 1022, 4059, 4091, 5412, 5455, 8118, 8119, 8183, 8192]:
+        for T in (1, 65, 1025):
+            assert s.segment(T, D) == 0
+    for T in (65, 2048, 100000):                # with the tile list of the fused kernel
+        for D in (1, 16, 127, 128):
+            s.option(F.WIDE_TILE, 2)
+            assert s.linear([256], 256, D, T) == 0
+    sorts = [l for l in s.launches() if l[0] == "segment_kernel"]
+    assert len(sorts) > 2000
+    assert max(lds for _, _, lds, _ in sorts) + static <= 65536, (static, max(lds for _, _, lds, _ in sorts))
+
+
+@pytest.mark.parametrize("scenario", [captured_orders, sorts_fit_lds], ids=lambda f: f.__name__)
 def test_host(scenario, tmp_path):
     F.run(__file__, scenario.__name__, tmp_path)
 

@@ -41,7 +41,9 @@
  * grow the workspace during a capture returns DZ_ERR_HIP and records nothing -- except base products
  * without deltas on more than 64 rows, which then cut k into the slices that fit the workspace as it is
  * (unless DZ_OPT_SPLIT_K gives their number): their fp32 sums may be added in another order than eagerly.
- * The fused kernel of base and deltas (DZ_OPT_WIDE_TILE) does the same; eagerly it may grow the workspace to 128 MB.
+ * The fused kernel of base and deltas (DZ_OPT_WIDE_TILE) does the same.  An eager call of it may replace the 32 MB of partial
+ * sums that dz_create allocates by 128 MB; if that much is refused it makes do with what there is, and the context does
+ * not ask again.
  * Otherwise all compute entry points only enqueue work on `stream` (a hipStream_t passed as
  * void*, NULL = the default stream) and return; nothing is synchronised except in dz_check and
  * dz_destroy.  One dz_ctx serves one stream at a time.  x and out must not overlap.

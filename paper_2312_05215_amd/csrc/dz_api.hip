@@ -84,9 +84,25 @@ static int capture_id(dz_ctx *ctx, hipStream_t st, unsigned long long &id)
 static int retire(dz_ctx *ctx, void *p)
 {
     if (!p) return DZ_OK;
-    if (ctx->n_retired >= (int)(sizeof(ctx->retired) / sizeof(ctx->retired[0]))) return DZ_ERR_LIMIT;
+    if (ctx->n_retired >= DZ_RETIRED) return DZ_ERR_LIMIT;
     ctx->retired[ctx->n_retired++] = p;
     return DZ_OK;
+}
+
+// A larger buffer for the partial sums.  The old one is retired only once the new one is there, and a refusal leaves nothing
+// behind: not in the context, and not in the runtime's last error, which the next launch would report as its own.
+static hipError_t grow_partial(dz_ctx *ctx, size_t bytes)
+{
+    void *p = nullptr;
+    const hipError_t e = hipMalloc(&p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return e;
+    }
+    (void)retire(ctx, ctx->partial);        // (the callers have looked for room)
+    ctx->partial = (float *)p;
+    ctx->partial_bytes = bytes;
+    return hipSuccess;
 }
 
 int dz_ensure_partial(dz_ctx *ctx, size_t bytes, hipStream_t st)
@@ -94,13 +110,20 @@ int dz_ensure_partial(dz_ctx *ctx, size_t bytes, hipStream_t st)
     if (bytes <= ctx->partial_bytes) return DZ_OK;
     if (ctx->static_ws) return DZ_ERR_LIMIT;
     if (int rc = quiesce_for_growth(ctx, st)) return rc;
-    if (int rc = retire(ctx, ctx->partial)) return rc;
-    ctx->partial = nullptr;
-    ctx->partial_bytes = 0;
-    size_t want = bytes + bytes / 4;
-    hipError_t e = hipMalloc((void **)&ctx->partial, want);
+    if (ctx->n_retired >= DZ_RETIRED) return DZ_ERR_LIMIT;
+    return dz_set_hip_error(ctx, grow_partial(ctx, bytes + bytes / 4));
+}
+
+// The same for a call that runs without it too, though slower: `bytes` and no more, not during a capture, and not again after a
+// refusal (a server whose HBM is full would otherwise pay for one on every call).
+int dz_want_partial(dz_ctx *ctx, size_t bytes, hipStream_t st)
+{
+    if (bytes <= ctx->partial_bytes || bytes >= ctx->partial_refused) return DZ_OK;
+    if (ctx->static_ws || ctx->n_retired >= DZ_RETIRED) return DZ_OK;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(st, &cs);
     if (e != hipSuccess) return dz_set_hip_error(ctx, e);
-    ctx->partial_bytes = want;
+    if (cs == hipStreamCaptureStatusNone && grow_partial(ctx, bytes) != hipSuccess) ctx->partial_refused = bytes;
     return DZ_OK;
 }
 

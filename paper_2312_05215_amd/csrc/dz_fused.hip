@@ -501,24 +501,21 @@ int dz_launch_fused(dz_ctx *ctx, const DzStreamArgs &args, const DzGroup &group,
     for (int p = gp.P; p <= DZ_MAX_GROUP; ++p) gp.rb_start[p] = NRB;
     int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
     cus = std::max(cus - cus % 8, 8);
-    // Partial tiles of the last round: two slots per compute unit at most.  A call that is being captured into a graph
-    // without an eager call before it cannot grow the workspace: the kernel cuts into as many slices as fit.
+    // the number of column tiles is known on the device only: enough workgroups for the most there can be
+    const long long most = (long long)NRB * dz_fused_tiles_max(a.T, a.D);
+    const int grid = (int)((most + 7) / 8 * 8 + 2 * cus);
+    // Partial tiles of the last round: as many as tail_slices can ask for, two slots per compute unit at most.  Where there is no
+    // memory for them, or the call is being captured into a graph without an eager call before it, the kernel cuts into
+    // as many slices as fit.
     constexpr size_t tile_bytes = (size_t)FR * FJ * FTHREADS * 16;
-    const size_t want = (size_t)2 * cus * tile_bytes;
-    if (want > ctx->partial_bytes) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        const hipError_t e = hipStreamIsCapturing(st, &cs);
-        if (e != hipSuccess) return dz_set_hip_error(ctx, e);
-        if (cs == hipStreamCaptureStatusNone)
-            if (int rc = dz_ensure_partial(ctx, want, st)) return rc;
-    }
+    const int tail = ((int)std::min(most, (long long)cus - 1) + 7) / 8 * 8;
+    const int S = std::min(a.K / 512, 8);
+    if (S > 1)
+        if (int rc = dz_want_partial(ctx, (size_t)std::min(2 * cus, tail * S) * tile_bytes, st)) return rc;
     const int slots = (int)std::min((size_t)2 * cus, ctx->partial_bytes / tile_bytes);
     if (int rc = dz_ensure_counters(ctx, cus, st)) return rc;
     a.partial = ctx->partial;
     a.counters = ctx->counters;
-    // the number of column tiles is known on the device only: enough workgroups for the most there can be
-    const long long most = (long long)NRB * dz_fused_tiles_max(a.T, a.D);
-    const int grid = (int)((most + 7) / 8 * 8 + 2 * cus);
     if (a.bits == 4 && a.group == 128) return dz_set_hip_error(ctx, launch_fused<4, 128>(a, gp, dp, ctx->seg_plan, NRB, cus, slots, grid, st));
     if (a.bits == 4) return dz_set_hip_error(ctx, launch_fused<4, 64>(a, gp, dp, ctx->seg_plan, NRB, cus, slots, grid, st));
     if (a.group == 128) return dz_set_hip_error(ctx, launch_fused<2, 128>(a, gp, dp, ctx->seg_plan, NRB, cus, slots, grid, st));

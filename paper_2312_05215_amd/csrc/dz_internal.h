@@ -6,6 +6,8 @@
 #include "../../include/dz.h"
 #include "dz_layout.h"
 
+#define DZ_RETIRED 64   /* buffers that growths of one context may replace */
+
 struct dz_ctx {
     int device = 0;
     // workspace (device memory owned by the context)
@@ -17,6 +19,7 @@ struct dz_ctx {
     struct DzFusedTile *seg_plan = nullptr;     // column tiles of the fused kernel for the present order (see DzFusedTile)
     float *partial = nullptr;       // split-K partial sums
     size_t partial_bytes = 0;
+    size_t partial_refused = SIZE_MAX;      // dz_want_partial: this much was refused
     int32_t *counters = nullptr;    // arrival counters, one per (chunk, row block); all zero between calls
     int counters_cap = 0;
     int32_t *err_flag = nullptr;    // sticky device-side error word
@@ -24,7 +27,7 @@ struct dz_ctx {
     size_t lora_u_bytes = 0;
     // Buffers a growth replaced.  A HIP graph recorded earlier may still hold their addresses in its
     // kernel nodes, so they stay allocated until dz_destroy.
-    void *retired[64] = {};
+    void *retired[DZ_RETIRED] = {};
     int n_retired = 0;
     bool static_ws = false;         // the workspace is the library's static device array: it never grows
     char hip_err[256] = {};
@@ -100,6 +103,7 @@ extern "C" int dz_run_linear(dz_ctx *ctx, const void *x, const void *W, const vo
                              const int32_t *ids, void *out, int T, int N, int K, int bits, int group, int accumulate,
                              bool has_base, bool has_delta, hipStream_t st);
 int dz_ensure_partial(dz_ctx *ctx, size_t bytes, hipStream_t st);
+int dz_want_partial(dz_ctx *ctx, size_t bytes, hipStream_t st);
 int dz_ensure_counters(dz_ctx *ctx, int n, hipStream_t st);
 int dz_ensure_lora(dz_ctx *ctx, size_t bytes, hipStream_t st);
 

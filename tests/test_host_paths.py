@@ -53,7 +53,41 @@ def sorts_fit_lds():
     assert max(lds for _, _, lds, _ in sorts) + static <= 65536, (static, max(lds for _, _, lds, _ in sorts))
 
 
-@pytest.mark.parametrize("scenario", [captured_orders, sorts_fit_lds], ids=lambda f: f.__name__)
+def memory_is_short():
+    """The fused kernel asks for the partial sums it can use, once, and runs with fewer where there is no memory for them."""
+    layer = ([5120] * 3, 5120, 16, 2048)
+    for K, T, grows in ((5120, 2048, True), (512, 2048, False), (5120, 100, False)):
+        s = F.Sim()
+        s.option(F.WIDE_TILE, 2)
+        before = s.fake.fake_live_bytes()
+        assert s.linear([5120] * 3 if T > 100 else [64], K, 16, T) == 0
+        assert s.fake.fake_live_bytes() - before == (128 << 20 if grows else 0), K     # (the replaced buffer stays)
+    s = F.Sim()
+    s.fake.fake_watch(b"fused_kernel", 6)       # the slots it may use
+    assert s.linear(*layer) == 0 and s.launches()[-1][::3] == ("fused_kernel", 512)
+    s = F.Sim()
+    s.room((128 << 20) - 1)
+    for _ in range(3):
+        assert s.linear(*layer) == 0
+        assert s.launches()[-1][::3] == ("fused_kernel", 128)
+    assert s.fake.fake_refused() == 1 and s.dz.dz_last_hip_error(s.ctx) == b""
+    s = F.Sim()
+    s.room(1 << 40)
+    s.capture(3)
+    assert s.linear(*layer) == 0 and s.launches()[-1][::3] == ("fused_kernel", 128)
+    s.capture(0)
+    assert s.linear(*layer) == 0 and s.launches()[-1][::3] == ("fused_kernel", 512)
+    # a call that cannot do without fails, and leaves the context as it was
+    s = F.Sim()
+    s.room(0)
+    s.option(F.SPLIT_K, 16)
+    assert s.linear([11008], 8192, 4, 1024) == -5
+    s.option(F.SPLIT_K, 0)
+    s.launches()
+    assert s.linear([4096], 4096, 4, 100) == 0 and s.kernels() == ["segment_kernel", "prefill_kernel"]
+
+
+@pytest.mark.parametrize("scenario", [captured_orders, sorts_fit_lds, memory_is_short], ids=lambda f: f.__name__)
 def test_host(scenario, tmp_path):
     F.run(__file__, scenario.__name__, tmp_path)
 

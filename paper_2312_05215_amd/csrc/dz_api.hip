@@ -377,10 +377,12 @@ static int run_group(dz_ctx *ctx, const void *x, int P, const void *const *W, co
         unsigned long long capture = 0;
         if (ctx->reuse_segments)
             if (int crc = capture_id(ctx, st, capture)) return crc;
-        const bool plan = tiled && dz_fused_takes(ctx, a, gp);
+        // The fused kernel wants its list of tiles with the order: also where only a later call of the layer may be its.
+        const bool fused = tiled && dz_fused_takes(ctx, a, gp);
         const bool same = ctx->reuse_segments && ctx->seg_ids == ids && ctx->seg_T == T && ctx->seg_D == D &&
-                          ctx->seg_capture == capture && (ctx->seg_planned || !plan);
+                          ctx->seg_capture == capture && (ctx->seg_planned || !fused);
         if (!same) {
+            const bool plan = fused || (tiled && ctx->reuse_segments && dz_fused_may_take(ctx, T, D));
             rc = dz_launch_segment(ctx, ids, T, D, nullptr, nullptr, ctx->seg_perm, ctx->seg_key, plan ? ctx->seg_plan : nullptr, st);
             if (rc) return rc;
             ctx->seg_ids = ids; ctx->seg_T = T; ctx->seg_D = D; ctx->seg_capture = capture; ctx->seg_planned = plan;

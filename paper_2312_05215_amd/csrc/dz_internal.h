@@ -130,6 +130,7 @@ int dz_launch_segment(dz_ctx *, const int32_t *ids, int T, int D, int32_t *count
 int dz_launch_stream(dz_ctx *, const DzStreamArgs &, const DzGroup &, const DzGroupPtrs &, hipStream_t);
 int dz_launch_prefill(dz_ctx *, const DzStreamArgs &, const DzGroup &, const DzGroupPtrs &, hipStream_t);
 int dz_launch_tile(dz_ctx *, const DzStreamArgs &, const DzGroup &, hipStream_t);
+bool dz_fused_may_take(const dz_ctx *, int T, int D);
 bool dz_fused_takes(const dz_ctx *, const DzStreamArgs &, const DzGroup &);
 int dz_launch_fused(dz_ctx *, const DzStreamArgs &, const DzGroup &, const DzGroupPtrs &, hipStream_t);
 bool dz_tile_fits(const DzStreamArgs &, const DzGroup &);

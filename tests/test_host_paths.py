@@ -87,7 +87,26 @@ def memory_is_short():
     assert s.linear([4096], 4096, 4, 100) == 0 and s.kernels() == ["segment_kernel", "prefill_kernel"]
 
 
-@pytest.mark.parametrize("scenario", [captured_orders, sorts_fit_lds, memory_is_short], ids=lambda f: f.__name__)
+def a_layer_shares_one_sort():
+    """DZ_OPT_REUSE_SEGMENTS: one sort serves the calls of a layer, whichever kernels they take and in whichever order."""
+    s = F.Sim()
+    seven_b = [([4096] * 3, 4096, "prefill_kernel"), ([4096], 4096, "prefill_kernel"), ([11008] * 2, 4096, "fused_kernel"),
+               ([4096], 11008, "prefill_kernel")]
+    for calls in (seven_b, seven_b[2:] + seven_b[:2]):
+        s.option(F.REUSE_SEGMENTS, 1)
+        for Ns, K, _ in calls:
+            assert s.linear(Ns, K, 8, 2048) == 0
+        assert s.kernels() == ["segment_kernel"] + [k for _, _, k in calls]
+    # routes that change between the calls: the list of tiles is made when it is first wanted
+    s.option(F.REUSE_SEGMENTS, 1)
+    for tile, kernels in ((0, ["segment_kernel", "prefill_kernel"]), (2, ["segment_kernel", "fused_kernel"]),
+                          (0, ["prefill_kernel"]), (2, ["fused_kernel"])):
+        s.option(F.WIDE_TILE, tile)
+        assert s.linear([4096], 4096, 8, 2048) == 0
+        assert s.kernels() == kernels
+
+
+@pytest.mark.parametrize("scenario", [captured_orders, sorts_fit_lds, memory_is_short, a_layer_shares_one_sort], ids=lambda f: f.__name__)
 def test_host(scenario, tmp_path):
     F.run(__file__, scenario.__name__, tmp_path)
 

@@ -510,14 +510,15 @@ int dz_launch_fused(dz_ctx *ctx, const DzStreamArgs &args, const DzGroup &group,
     // the number of column tiles is known on the device only: enough workgroups for the most there can be
     const long long most = (long long)NRB * dz_fused_tiles_max(a.T, a.D);
     const int grid = (int)((most + 7) / 8 * 8 + 2 * cus);
-    // Partial tiles of the last round: as many as tail_slices can ask for, two slots per compute unit at most.  Where there is no
-    // memory for them, or the call is being captured into a graph without an eager call before it, the kernel cuts into
-    // as many slices as fit.
+    // Partial tiles of the last round: tail * S is the most that tail_slices can ask for.  A call that needs more room than
+    // there is makes room for every later one, two slots per compute unit: the workspace grows once.  Where that much memory is
+    // not to be had, or the call is being captured into a graph without an eager call before it, the kernel cuts into as many
+    // slices as fit.
     constexpr size_t tile_bytes = (size_t)FR * FJ * FTHREADS * 16;
     const int tail = ((int)std::min(most, (long long)cus - 1) + 7) / 8 * 8;
     const int S = std::min(a.K / 512, 8);
-    if (S > 1)
-        if (int rc = dz_want_partial(ctx, (size_t)std::min(2 * cus, tail * S) * tile_bytes, st)) return rc;
+    if (S > 1 && (size_t)std::min(2 * cus, tail * S) * tile_bytes > ctx->partial_bytes)
+        if (int rc = dz_want_partial(ctx, (size_t)2 * cus * tile_bytes, st)) return rc;
     const int slots = (int)std::min((size_t)2 * cus, ctx->partial_bytes / tile_bytes);
     if (int rc = dz_ensure_counters(ctx, cus, st)) return rc;
     a.partial = ctx->partial;

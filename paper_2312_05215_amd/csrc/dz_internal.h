@@ -6,7 +6,9 @@
 #include "../../include/dz.h"
 #include "dz_layout.h"
 
-#define DZ_RETIRED 64   /* buffers that growths of one context may replace */
+// Buffers that growths of one context may replace: 64, the tile list of each growth of the sorted order (capacity from
+// 4096 rows on at least doubles each time, and x has less than 2^22 rows: ten), and the growth of the fused kernel's partial sums.
+#define DZ_RETIRED 75
 
 struct dz_ctx {
     int device = 0;

@@ -83,3 +83,8 @@ class Sim:
         deltas = (ctypes.c_void_p * max(P * D, 1))(*[0x100000000 + 0x1000000 * m for m in range(P * D)])
         return self.dz.dz_linear_group(self.ctx, ctypes.c_void_p(0x20000), P, W, deltas, D, ctypes.c_void_p(ids), out,
                                        (ctypes.c_int * P)(*Ns), T, K, bits, group, STREAM)
+
+    def lora(self, T, rank=8):
+        one = (ctypes.c_void_p * 1)(0x40000)
+        return self.dz.dz_lora_sbmm(self.ctx, ctypes.c_void_p(0x20000), one, one, 1, rank, ctypes.c_void_p(0x10000),
+                                    ctypes.c_void_p(0x50000), T, 16, 256, 0, STREAM)

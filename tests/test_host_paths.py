@@ -106,7 +106,26 @@ def a_layer_shares_one_sort():
         assert s.kernels() == kernels
 
 
-@pytest.mark.parametrize("scenario", [captured_orders, sorts_fit_lds, memory_is_short, a_layer_shares_one_sort], ids=lambda f: f.__name__)
+def growths_are_not_used_up():
+    """A context may grow the sorted order from 4096 rows to the most that x can have, the fused kernel's partial sums, and
+    the adapters' buffer 44 times.  The partial sums grow once, whatever the sizes of the calls."""
+    s, T = F.Sim(), 4097
+    s.option(F.WIDE_TILE, 2)
+    before = s.fake.fake_live_bytes()
+    for N in range(4096, 16384, 256):
+        assert s.linear([N], 4096, 1, 512) == 0
+    assert s.fake.fake_live_bytes() - before == 128 << 20
+    s.option(F.WIDE_TILE, 0)
+    while T < 1 << 22:
+        assert s.linear([16], 256, 1, T) == 0, T
+        T = 2 * T + 1
+    rows = 8
+    for i in range(45):
+        assert s.lora(rows) == 0, i
+        rows = rows * 5 // 4 + 1
+
+
+@pytest.mark.parametrize("scenario", [captured_orders, sorts_fit_lds, memory_is_short, a_layer_shares_one_sort, growths_are_not_used_up], ids=lambda f: f.__name__)
 def test_host(scenario, tmp_path):
     F.run(__file__, scenario.__name__, tmp_path)
 

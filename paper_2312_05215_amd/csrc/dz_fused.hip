@@ -493,6 +493,21 @@ bool dz_fused_takes(const dz_ctx *ctx, const DzStreamArgs &a, const DzGroup &gp)
     return e < 0.95f * narrow_estimate((int)NRB, a.T, a.D, KT, cus);
 }
 
+// Does a call of base and 2:4 deltas with the default options come here?  For callers that name the kernel they time.
+extern "C" int dz_fused_route(int P, const int *N, int T, int K, int D, int cus)
+{
+    if (P < 1 || P > DZ_MAX_GROUP) return 0;
+    dz_ctx ctx;
+    ctx.num_cus = cus;
+    DzStreamArgs a = {};
+    a.T = T; a.K = K; a.D = D;
+    a.has_base = 1; a.has_delta = D > 0;
+    DzGroup gp = {};
+    gp.P = P;
+    for (int p = 0; p < P; ++p) gp.N[p] = N[p];
+    return dz_fused_takes(&ctx, a, gp) ? 1 : 0;
+}
+
 int dz_launch_fused(dz_ctx *ctx, const DzStreamArgs &args, const DzGroup &group, const DzGroupPtrs &dp, hipStream_t st)
 {
     DzStreamArgs a = args;

@@ -45,13 +45,14 @@ __device__ inline int place(int32_t *cur, int key, bool active, int key_bits, in
 // waits for the next segment unless it has ten blocks by itself and the next one does not fit whole: a step costs six
 // blocks' time beside the blocks', so few wide tiles are the cheapest.  (Lists for nine narrower limits as well, for each
 // launch to choose the one that fills its last round best, brought less than the pass grew by: 5 to 10 us.)
-__device__ void plan_tiles(const int32_t *start, int T, int D, DzFusedTile *plan)
+__host__ __device__ void plan_tiles(const int32_t *start, int T, int D, DzFusedTile *plan)
 {
     constexpr int CAP = DZ_FUSED_BLOCKS;
     int n = 0, most = 0, o_start = 0, o_rows = 0, o_key = 0;        // the open tile's first segment, if it has rows
     auto emit = [&](int s0, int r0, int k0, int s1, int r1, int k1) {
         plan[++n] = DzFusedTile{s0, r0, k0, s1, r1, k1, {0, 0}};
-        most = max(most, dz_fused_cost((r1 ? (r0 + 31) >> 5 << 1 : (r0 + 15) >> 4) + ((r1 + 15) >> 4)));
+        const int cost = dz_fused_cost((r1 ? (r0 + 31) >> 5 << 1 : (r0 + 15) >> 4) + ((r1 + 15) >> 4));
+        most = cost > most ? cost : most;
     };
     for (int key = 0; key <= D; ++key) {
         int at = start[key], rows = (key < D ? start[key + 1] : T) - at;
@@ -184,4 +185,12 @@ int dz_launch_segment(dz_ctx *ctx, const int32_t *ids, int T, int D, int32_t *co
     hipLaunchKernelGGL(segment_kernel, dim3(1), dim3(SEG_THREADS), lds, st, ids, T, D, runs, key_bits, counts, offsets, perm, key,
                        plan, ctx->err_flag);
     return dz_set_hip_error(ctx, hipGetLastError());
+}
+
+// The list that a sort leaves where key d begins at start[d] (start[D]: the rows of the base model), for tests without a GPU:
+// its head and tiles.  Returns the most tiles there can be, which is what the workspace and the grid are sized for.
+extern "C" int dz_fused_list(const int32_t *start, int T, int D, DzFusedTile *list)
+{
+    if (list) plan_tiles(start, T, D, list);
+    return dz_fused_tiles_max(T, D);
 }

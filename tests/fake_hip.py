@@ -1,6 +1,7 @@
 """libdz's host side on a HIP runtime without a GPU (fake_hip.cpp): which kernels a call launches, with what memory.
 Has to be used in a process of its own that has loaded no other HIP library: see `run`."""
 import ctypes
+import json
 import os
 import subprocess
 import sys
@@ -11,13 +12,17 @@ SPLIT_K, WIDE_TILE, REUSE_SEGMENTS = 1, 5, 6        # option keys of include/dz.
 STREAM = ctypes.c_void_p(0x30000)                  # (the default stream cannot be captured)
 
 
-def run(test_file, scenario, tmp_path):
+def run(test_file, scenario, tmp_path, data=None):
     """Call function `scenario` of `test_file` in a new process, with the fake runtime built under `tmp_path`."""
     so = os.path.join(str(tmp_path), "libfake_hip.so")
     subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "fake_hip.cpp")], check=True)
-    p = subprocess.run([sys.executable, test_file, scenario], env=dict(os.environ, FAKE_HIP=so), text=True,
+    p = subprocess.run([sys.executable, test_file, scenario], env=dict(os.environ, FAKE_HIP=so, FAKE_HIP_DATA=json.dumps(data)), text=True,
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, timeout=120)
     assert p.returncode == 0, p.stdout
+
+
+def data():
+    return json.loads(os.environ["FAKE_HIP_DATA"])
 
 
 def static_lds(kernel):

@@ -86,3 +86,50 @@ def test_group_captured_and_replayed_with_other_segments(dz):
             assert dz.dz_check(c.h) == dz.DZ_OK
             for p, cs in enumerate(cases):
                 _check(outs[p], cs, x, ids, f"replay {rep} projection {p}")
+
+
+@pytest.mark.parametrize("bits,G", [(2, 64), (4, 64)])
+def test_full_rounds_and_a_sliced_rest(dz, bits, G):
+    """More tiles than CUs: whole ones first, then the tiles of the last round cut into slices of k of two and three k tiles."""
+    from test_fused_plan import _list
+    print(f"fused rounds {bits} {G}", flush=True)
+    N, K, lengths = 8192, 1280, [20, 17, 1, 33, 16, 20, 30, 2, 9, 20, 20, 31, 32, 5, 20, 20, 28, 20]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count // 8 * 8
+    tiles = N // 256 * int(_list(lengths, 0)[0][0])
+    assert tiles > cus and 0 < tiles % cus <= 64
+    ids = _ids(lengths)
+    with dz.Context(0) as c:
+        c.set_option(dz.DZ_OPT_WIDE_TILE, 2)
+        cs = Case(dz, c.h, 32, len(ids), N, K, len(lengths), bits, G, ids)
+        for rep in range(2):                     # the arrival counters are ready again
+            o = cs.out(fill=7.0)
+            dz.dz_linear(c.h, cs.dx, cs.dW, cs.packed, cs.dids, o, cs.T, N, K, bits, G)
+            assert dz.dz_check(c.h) == dz.DZ_OK
+            _check(o, cs, cs.x, ids, f"rounds {rep}")
+
+
+def test_captured_cold_and_replayed_after_the_workspace_grew(dz):
+    """The first call of a context is a captured one: its slices of k fit the partial sums as dz_create made them (128 partial
+    tiles; an eager call grows them and may cut finer).  Replays with other segments, before and after that growth."""
+    T, N, K, D = 512, 4096, 4096, 2
+    print("fused cold capture", flush=True)
+    with dz.Context(0) as c:
+        c.set_option(dz.DZ_OPT_WIDE_TILE, 2)
+        cs = Case(dz, c.h, 33, T, N, K, D, 4, 128, _ids([300, 200], 12))
+        dx, dids, o = cs.dx, cs.dids, cs.out(fill=7.0)
+
+        def call():
+            dz.dz_linear(c.h, dx, cs.dW, cs.packed, dids, o, T, N, K, 4, 128)
+
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            call()
+        for rep, (lengths, base) in enumerate([([300, 200], 12), ([0, 512], 0), ([17, 1], 494)]):
+            x, ids = S.make_x(T, K, S.stream(95 + rep, "x")), _ids(lengths, base)
+            dx.copy_(x)
+            dids.copy_(torch.from_numpy(ids))
+            for what, f in (("replay", graph.replay), ("eager", call)):
+                o.fill_(7.0)
+                f()
+                assert dz.dz_check(c.h) == dz.DZ_OK
+                _check(o, cs, x, ids, f"{what} {rep}")

@@ -377,15 +377,18 @@ static int run_group(dz_ctx *ctx, const void *x, int P, const void *const *W, co
         unsigned long long capture = 0;
         if (ctx->reuse_segments)
             if (int crc = capture_id(ctx, st, capture)) return crc;
-        // The fused kernel wants its list of tiles with the order: also where only a later call of the layer may be its.
-        const bool fused = tiled && dz_fused_takes(ctx, a, gp);
-        const bool same = ctx->reuse_segments && ctx->seg_ids == ids && ctx->seg_T == T && ctx->seg_D == D &&
-                          ctx->seg_capture == capture && (ctx->seg_planned || !fused);
+        // The fused kernel wants its list of tiles with the order.  Where another kernel's call has made the order, the list is
+        // made from its offsets.
+        const bool plan = tiled && dz_fused_takes(ctx, a, gp);
+        const bool same = ctx->reuse_segments && ctx->seg_ids == ids && ctx->seg_T == T && ctx->seg_D == D && ctx->seg_capture == capture;
         if (!same) {
-            const bool plan = fused || (tiled && ctx->reuse_segments && dz_fused_may_take(ctx, T, D));
-            rc = dz_launch_segment(ctx, ids, T, D, nullptr, nullptr, ctx->seg_perm, ctx->seg_key, plan ? ctx->seg_plan : nullptr, st);
+            rc = dz_launch_segment(ctx, ids, T, D, nullptr, ctx->seg_offsets, ctx->seg_perm, ctx->seg_key, plan ? ctx->seg_plan : nullptr, st);
             if (rc) return rc;
             ctx->seg_ids = ids; ctx->seg_T = T; ctx->seg_D = D; ctx->seg_capture = capture; ctx->seg_planned = plan;
+        } else if (plan && !ctx->seg_planned) {
+            rc = dz_launch_fused_list(ctx, T, D, st);
+            if (rc) return rc;
+            ctx->seg_planned = true;
         }
         a.perm = ctx->seg_perm;
         a.key = ctx->seg_key;

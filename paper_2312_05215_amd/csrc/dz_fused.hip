@@ -468,17 +468,10 @@ static float narrow_estimate(int NRB, int T, int D, int KT, int cus)
 // geometric mean, two of them slower (1127 x 5120 x 5120, eight uneven deltas, 151 us there and 157 here, is the worst).  64 rows
 // a delta and 10 %, without the two tiles, takes 155 of the 355, but 28 of them are slower, the worst 1.40 times.
 // DZ_OPT_WIDE_TILE = 2 leaves the estimate out.
-// dz_fused_may_take is the part of it that holds for all projections of a layer.
-bool dz_fused_may_take(const dz_ctx *ctx, int T, int D)
-{
-    if (!ctx->tile_kernel || ctx->force_splits > 0 || T <= 64 || D > DZ_MAX_DELTAS) return false;
-    return ctx->tile_kernel == 2 || T >= 128 * D;
-}
-
 bool dz_fused_takes(const dz_ctx *ctx, const DzStreamArgs &a, const DzGroup &gp)
 {
-    if (!dz_fused_may_take(ctx, a.T, a.D) || !a.has_base || !a.has_delta || a.quant_only) return false;
-    if ((unsigned long long)a.T * a.K * 2ull >= (1ull << 31)) return false;
+    if (!ctx->tile_kernel || ctx->force_splits > 0 || !a.has_base || !a.has_delta || a.quant_only || a.T <= 64) return false;
+    if (a.D > DZ_MAX_DELTAS || (unsigned long long)a.T * a.K * 2ull >= (1ull << 31)) return false;
     long long NRB = 0;
     for (int p = 0; p < gp.P; ++p) {
         if ((unsigned long long)gp.N[p] * a.K * 2ull >= (1ull << 31)) return false;
@@ -488,6 +481,7 @@ bool dz_fused_takes(const dz_ctx *ctx, const DzStreamArgs &a, const DzGroup &gp)
     if (ctx->tile_kernel == 2) return true;
     int cus = ctx->num_cus > 0 ? ctx->num_cus : 256;
     cus = std::max(cus - cus % 8, 8);
+    if (a.T < 128 * a.D) return false;
     const int KT = a.K / 256;
     const float e = std::max(fused_estimate((int)NRB, a.T, a.D, KT, cus, 0), fused_estimate((int)NRB, a.T, a.D, KT, cus, 2));
     return e < 0.95f * narrow_estimate((int)NRB, a.T, a.D, KT, cus);

@@ -16,7 +16,7 @@ struct dz_ctx {
     int32_t *seg_perm = nullptr;    // [seg_cap] request indices in delta-sorted order
     int32_t *seg_key = nullptr;     // [seg_cap] delta index of each sorted position (D = none)
     int32_t *seg_counts = nullptr;  // [DZ_SEG_MAX_D + 1]
-    int32_t *seg_offsets = nullptr; // [DZ_SEG_MAX_D + 2]
+    int32_t *seg_offsets = nullptr; // [DZ_SEG_MAX_D + 2] first sorted position of each delta, then of the rows without one
     int seg_cap = 0;
     struct DzFusedTile *seg_plan = nullptr;     // column tiles of the fused kernel for the present order (see DzFusedTile)
     float *partial = nullptr;       // split-K partial sums
@@ -132,7 +132,7 @@ int dz_launch_segment(dz_ctx *, const int32_t *ids, int T, int D, int32_t *count
 int dz_launch_stream(dz_ctx *, const DzStreamArgs &, const DzGroup &, const DzGroupPtrs &, hipStream_t);
 int dz_launch_prefill(dz_ctx *, const DzStreamArgs &, const DzGroup &, const DzGroupPtrs &, hipStream_t);
 int dz_launch_tile(dz_ctx *, const DzStreamArgs &, const DzGroup &, hipStream_t);
-bool dz_fused_may_take(const dz_ctx *, int T, int D);
+int dz_launch_fused_list(dz_ctx *, int T, int D, hipStream_t);
 bool dz_fused_takes(const dz_ctx *, const DzStreamArgs &, const DzGroup &);
 int dz_launch_fused(dz_ctx *, const DzStreamArgs &, const DzGroup &, const DzGroupPtrs &, hipStream_t);
 bool dz_tile_fits(const DzStreamArgs &, const DzGroup &);

@@ -69,7 +69,7 @@ class Sim:
         out = []
         for i in range(self.fake.fake_launches()):
             name = self.fake.fake_name(i).decode()
-            short = next(k for k in ("segment_kernel", "fused_kernel", "prefill_kernel", "tile_kernel", "stream_kernel", "shrink", "expand",
+            short = next(k for k in ("segment_kernel", "fused_list_kernel", "fused_kernel", "prefill_kernel", "tile_kernel", "stream_kernel", "shrink", "expand",
                                      "clear", "") if k in name)
             out.append((short or name, self.fake.fake_grid(i), self.fake.fake_lds(i), self.fake.fake_watched(i)))
         self.fake.fake_clear()

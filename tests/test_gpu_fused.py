@@ -133,3 +133,19 @@ def test_captured_cold_and_replayed_after_the_workspace_grew(dz):
                 f()
                 assert dz.dz_check(c.h) == dz.DZ_OK
                 _check(o, cs, x, ids, f"{what} {rep}")
+
+
+@pytest.mark.parametrize("case", [CASES[1], CASES[4], CASES[6]], ids=lambda c: c[0])
+def test_list_of_an_order_that_another_kernel_s_call_made(dz, case):
+    name, N, K, bits, G, lengths, base = case
+    print(f"fused list {name}", flush=True)
+    ids = _ids(lengths, base)
+    with dz.Context(0) as c:
+        cs = Case(dz, c.h, 34, len(ids), N, K, len(lengths), bits, G, ids)
+        c.set_option(dz.DZ_OPT_REUSE_SEGMENTS, 1)
+        for route in (0, 2, 0, 2):
+            c.set_option(dz.DZ_OPT_WIDE_TILE, route)
+            o = cs.out(fill=7.0)
+            dz.dz_linear(c.h, cs.dx, cs.dW, cs.packed, cs.dids, o, cs.T, N, K, bits, G)
+            assert dz.dz_check(c.h) == dz.DZ_OK
+            _check(o, cs, cs.x, ids, f"{name} route {route}")

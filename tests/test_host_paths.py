@@ -88,18 +88,20 @@ def memory_is_short():
 
 
 def a_layer_shares_one_sort():
-    """DZ_OPT_REUSE_SEGMENTS: one sort serves the calls of a layer, whichever kernels they take and in whichever order."""
+    """DZ_OPT_REUSE_SEGMENTS: one sort serves the calls of a layer, whichever kernels they take and in whichever order; the
+    list of the fused kernel is made once, with the sort or from it, and only where a call wants it."""
     s = F.Sim()
     seven_b = [([4096] * 3, 4096, "prefill_kernel"), ([4096], 4096, "prefill_kernel"), ([11008] * 2, 4096, "fused_kernel"),
                ([4096], 11008, "prefill_kernel")]
-    for calls in (seven_b, seven_b[2:] + seven_b[:2]):
+    for calls, at in ((seven_b + seven_b[2:], 2), (seven_b[2:] + seven_b, 0), (seven_b[:2], 9)):
         s.option(F.REUSE_SEGMENTS, 1)
         for Ns, K, _ in calls:
             assert s.linear(Ns, K, 8, 2048) == 0
-        assert s.kernels() == ["segment_kernel"] + [k for _, _, k in calls]
+        want = [k for _, _, k in calls]
+        assert s.kernels() == ["segment_kernel"] + (want if at in (0, 9) else want[:at] + ["fused_list_kernel"] + want[at:])
     # routes that change between the calls: the list of tiles is made when it is first wanted
     s.option(F.REUSE_SEGMENTS, 1)
-    for tile, kernels in ((0, ["segment_kernel", "prefill_kernel"]), (2, ["segment_kernel", "fused_kernel"]),
+    for tile, kernels in ((0, ["segment_kernel", "prefill_kernel"]), (2, ["fused_list_kernel", "fused_kernel"]),
                           (0, ["prefill_kernel"]), (2, ["fused_kernel"])):
         s.option(F.WIDE_TILE, tile)
         assert s.linear([4096], 4096, 8, 2048) == 0

@@ -15,7 +15,7 @@ A default run (no --workload) times the headline workload and then, more briefly
 performance configurations, whose figures go into the `workloads` object of the same JSON line:
 7b_decode_many (32 deltas, 2-bit, Zipf ids, 64 rows, all 32 layers resident), 70b_stack (Llama-70B
 shapes, 4 deltas, 2-bit, 64 rows, all 80 layers = 214 GB resident) and 13b_prefill (2048 request
-rows in 16 prompt segments, all 40 layers resident; runs the tiled MFMA kernel and is priced against
+rows in 16 prompt segments, all 40 layers resident; runs a tiled MFMA kernel and is priced against
 the fp16 MFMA peak instead of HBM).  `--workload X` times X alone as the primary figure.
 
 Prints ONE JSON line.  value = request rows (tokens) per second through the whole stack of layers;
@@ -87,6 +87,16 @@ def profile_traffic(kernel: str, workload: str, launches_per_layer: int):
     except (OSError, ValueError):
         pass
     return None, None
+
+
+def tiled_kernel(launches, T: int, D: int, cus: int) -> str:
+    """The kernel that base + delta launches of more than 64 rows go to; launches: [(output sizes, K)].  "fused_kernel" or
+    "prefill_kernel" where all of them take the same one, else both."""
+    import ctypes
+    import paper_2312_05215_amd as dz
+    route = dz.lib().dz_fused_route
+    names = {"fused_kernel" if route(len(Ns), (ctypes.c_int * len(Ns))(*Ns), T, K, D, cus) else "prefill_kernel" for Ns, K in launches}
+    return " and ".join(sorted(names))
 
 
 def run_workload(args, name, steps, warmup, with_cpu, primary):
@@ -219,22 +229,24 @@ def run_workload(args, name, steps, warmup, with_cpu, primary):
                                     for _, N, K in projs)
     avg_launch_us = ms_per_step * 1e3 / launches_per_step
     achieved = bytes_per_step / (ms_per_step * 1e-3) / 1e9
-    traffic, traffic_src = (profile_traffic("stream_kernel" if cfg.T <= 64 else "prefill_kernel", cfg.name, launches_per_layer)
-                            if path == "linear" else (None, None))
+    launches = [([projs[i][1] for i in g], projs[g[0]][2]) for g in (groups if grouped else [[i] for i in range(len(projs))])]
+    fused_name = "stream_kernel" if cfg.T <= 64 else tiled_kernel(launches, cfg.T, cfg.D,
+                                                                  torch.cuda.get_device_properties(0).multi_processor_count)
+    traffic, traffic_src = profile_traffic(fused_name, cfg.name, launches_per_layer) if path == "linear" else (None, None)
     roofline = {"bound": "hbm", "kernel": "stream_kernel (fused base GEMM + SBMM)", "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "traffic_source": traffic_src,
                 "bytes_per_launch_avg": bytes_per_step // launches_per_step,
                 "avg_launch_us": round(avg_launch_us, 2), "launches_per_step": launches_per_step}
     if cfg.T > 64:
-        # large batches run the tiled MFMA kernel: 2*T*N*K flops of the base product plus 2*T*N*K/2 of the
+        # large batches run a tiled MFMA kernel: 2*T*N*K flops of the base product plus 2*T*N*K/2 of the
         # 2:4-sparse delta product for every request row that names a delta
         rows_with_delta = int(((ids >= 0) & (ids < cfg.D)).sum())
         dense_rows = 0 if path == "sbmm" else cfg.T
         sparse_rows = 0 if path == "base" else rows_with_delta
         flops_per_step = n_layers * sum(2.0 * N * K * (dense_rows + 0.5 * sparse_rows) for _, N, K in projs)
         tf = flops_per_step / (ms_per_step * 1e-3) / 1e12
-        kname = {"linear": "prefill_kernel (fused base GEMM + SBMM)", "base": "tile_kernel (base GEMM)",
+        kname = {"linear": fused_name + " (fused base GEMM + SBMM)", "base": "tile_kernel (base GEMM)",
                  "sbmm": "prefill_kernel (SBMM)"}[path]
         roofline = {"bound": "mfma", "kernel": kname, "achieved": round(tf, 1),
                     "peak": MFMA_F16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(tf / MFMA_F16_PEAK_TFLOPS, 4),

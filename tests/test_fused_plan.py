@@ -75,6 +75,22 @@ def test_the_rule(route):
     assert dz.lib().dz_fused_route(len(Ns), (ctypes.c_int * len(Ns))(*Ns), T, K, D, 256) == fused
 
 
+def test_the_benchmark_names_the_kernel_that_runs_and_its_traffic():
+    import bench
+    import dz_synth as S
+    cfg = S.config("13b_prefill")
+    projs = S.projections_of(cfg)
+    for groups, MB in ((S.launch_groups(cfg), 2140), ([[i] for i in range(len(projs))], 1107)):
+        launches = [([projs[i][1] for i in g], projs[g[0]][2]) for g in groups]
+        kernel = bench.tiled_kernel(launches, cfg.T, cfg.D, 256)
+        assert kernel == "fused_kernel"
+        traffic, src = bench.profile_traffic(kernel, cfg.name, len(launches))
+        assert src == "profiles/fused_kernel_13b_prefill_pmc.txt" and traffic // 10 ** 6 == MB
+    both = bench.tiled_kernel([([11008] * 2, 4096), ([4096], 4096)], 2048, 8, 256)
+    assert both == "fused_kernel and prefill_kernel"
+    assert bench.profile_traffic(both, cfg.name, 4) == (None, None)
+
+
 def launched():
     """The calls of test_gpu_fused.py and of ROUTES launch the kernel that they are about."""
     data = F.data()

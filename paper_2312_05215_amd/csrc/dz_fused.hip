@@ -2,10 +2,9 @@
 //
 //   out[t] = f16( x[t] . W^T + x[t] . Delta_{Idx[t]}^T )      (paper Section 5.1 Eq. (2); Section 5.2)
 //
-// Where a delta has dozens of request rows the product is bound by the matrix pipes, and on a full chip by the power that
-// they draw.  The narrower tiled kernel keeps them 37 to 44 % busy there (13824 x 5120, T = 2048): its 256 x 128 tile brings in
-// a byte of W per 128 request rows, straight from global memory in 64-byte pieces, and dequantises a packed tile for every
-// segment of each 128 rows.  Here
+// Where a delta has dozens of request rows the product is bound by the matrix pipes.  The narrower tiled kernel keeps them 40 %
+// busy on a 13B layer of T = 2048 and 16 deltas: its 256 x 128 tile brings in a byte of W per 128 request rows, straight from
+// global memory in 64-byte pieces, and dequantises a packed tile for every segment of each 128 rows.  Here
 //   * a workgroup (8 waves) owns 256 rows of N x up to 256 request rows; a wave owns 2 row tiles x 16 column blocks (128
 //     accumulator registers), so a packed tile is dequantised once for all its columns, and every fragment of x that a
 //     wave reads from LDS feeds four dense and two sparse MFMAs;
@@ -20,8 +19,10 @@
 //     64 of them a step).  One barrier ends each half;
 //   * packed tiles wait in stage registers, loaded a step before they are needed.
 // us, 13824 x 5120, T = 2048, narrower kernel -> here (medians of seven turns): one delta 438 -> 384 (the rule below still leaves
-// that call to the narrower kernel), 8 segments of 256 rows 459 -> 402, 16 of 128 469 -> 434, 16 random ones 517 -> 483;
-// 777 x (2 x 11008) x 4096, 3 deltas 257 -> 242 (left there too).  The chip runs at 1.5 to 1.8 GHz on random values, at 2.3 GHz on zeros.
+// that call to the narrower kernel), 8 segments of 256 rows 459 -> 402, 16 of 128 469 -> 434, 16 random ones 517 -> 483.  The launches
+// of that 13B layer: q,k,v 662 -> 613, o 233 -> 218, gate,up 1151 -> 1087, down 577 -> 530; of a 7B layer of 777 rows and three 2-bit
+// deltas, which the rule leaves to the narrower kernel: 168 -> 153, 70 -> 70, 281 -> 257, 158 -> 137.  On the 13B layer the pipes are
+// busy 44 % of the time at some 1.9 GHz (nominal 2.4), waves wait for operands 34 % of theirs, and a launch moves 2.1 GB (2.5 before).
 #include "dz_mma.h"
 #include <algorithm>
 #include <cmath>
